@@ -349,20 +349,27 @@ hipError_t batch_launch(const void* table, const int* bstart, int nm, unsigned b
   return hipGetLastError();
 }
 
+// With a record open, append a launch (argument block a, its batched form, and
+// that form's block size and LDS) and return true.
+template <typename A>
+bool launch_recorded(const A& a, BatchLaunch batched, unsigned blocks, unsigned threads, size_t smem) {
+  std::vector<LaunchRecord>* rec = launch_record();
+  if (!rec) return false;
+  LaunchRecord r;
+  r.launch = batched;
+  r.args.assign(reinterpret_cast<const unsigned char*>(&a), reinterpret_cast<const unsigned char*>(&a) + sizeof(A));
+  r.blocks = blocks;
+  r.threads = threads;
+  r.smem = smem;
+  rec->push_back(std::move(r));
+  return true;
+}
+
 // Launch kernel K (argument block a) or, with a record open, record it with
 // its batched form KB.
 template <typename A, void (*K)(A), void (*KB)(const A*, const int*, int)>
 hipError_t launch(const A& a, unsigned blocks, unsigned threads, size_t smem, hipStream_t s) {
-  if (std::vector<LaunchRecord>* rec = launch_record()) {
-    LaunchRecord r;
-    r.launch = &batch_launch<A, KB>;
-    r.args.assign(reinterpret_cast<const unsigned char*>(&a), reinterpret_cast<const unsigned char*>(&a) + sizeof(A));
-    r.blocks = blocks;
-    r.threads = threads;
-    r.smem = smem;
-    rec->push_back(std::move(r));
-    return hipSuccess;
-  }
+  if (launch_recorded(a, &batch_launch<A, KB>, blocks, threads, smem)) return hipSuccess;
   if (blocks == 0) return hipSuccess;
   hipLaunchKernelGGL(K, dim3(blocks), dim3(threads), smem, s, a);
   return hipGetLastError();

@@ -1,0 +1,10 @@
+// The strided forward passes in float64, every length of regfft.h.
+#include "regfft.h"
+
+namespace jgb {
+namespace fft {
+
+JGB_REG_INSTANTIATE(double, RP_FWD, JGB_REG_LENGTHS_F64)
+
+}  // namespace fft
+}  // namespace jgb

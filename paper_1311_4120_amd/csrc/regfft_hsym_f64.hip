@@ -1,0 +1,10 @@
+// The inverse's first pass in float64, every length of regfft.h.
+#include "regfft.h"
+
+namespace jgb {
+namespace fft {
+
+JGB_REG_INSTANTIATE(double, RP_HSYM, JGB_REG_LENGTHS_F64)
+
+}  // namespace fft
+}  // namespace jgb
