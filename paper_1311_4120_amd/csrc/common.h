@@ -263,7 +263,7 @@ struct Plan {
   double win[2] = {0.0, 0.0};      // 3D: (a, 0); 2D: (R0, R1)
   int* d_touched = nullptr;        // gather tiles some node touches
   int ntouched = 0;
-  unsigned char* d_tflag = nullptr;  // per gather tile: 1 if touched
+  unsigned char* d_tflag = nullptr;  // per gather tile: 1 if touched; then per tile column along the paired passes' axis
   int* d_ublocks = nullptr;        // logical blocks of the unmix pass (fft.hip)
   int nublocks = 0;
   double* d_splitk = nullptr;      // per internal axis a: k_a(q) for q < nf_a, then exp(-k_a(q)^2 / a)

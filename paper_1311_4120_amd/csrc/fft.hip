@@ -30,7 +30,7 @@
 #include <algorithm>
 #include <cmath>
 
-#include "regfft.h"
+#include "regpair.h"
 
 namespace jgb {
 
@@ -58,8 +58,6 @@ __global__ void __launch_bounds__(NT) k_fft_pass(PassArgs<T> a) {
 // reads the N-point inputs instead of the L-point spectrum.  Every line is
 // owned by one block; a line that is its own mirror sits in two rows of its
 // block, which end up equal.  Registers are capped at 128 (four waves per SIMD).
-enum PairMode { PAIR_UNMIX = 0, PAIR_FUSED = 1 };
-
 template <typename T, int MODE, int MAXV, int NT>
 __global__ void __launch_bounds__(NT, 4) k_fft_pair_pass(PassArgs<T> a) {
   extern __shared__ unsigned char smem_raw[];
@@ -501,8 +499,8 @@ unsigned pair_geometry(PassArgs<T>& a) {
       Ns *= a.rad[st];
     }
   }
-  const int lb = lines_per_block<T>(a.L);
-  a.P = lb / 2 > 0 ? lb / 2 : 1;
+  const int lb = lines_per_block<T>(a.L), own = a.dim3 ? reg_pair_lines<T>(a.L) : 0;
+  a.P = own > 0 ? own : lb / 2 > 0 ? lb / 2 : 1;
   a.LB = 2 * a.P;
   a.dLB = FastDiv((uint32_t)a.LB);
   a.dP = FastDiv((uint32_t)a.P);
@@ -519,6 +517,13 @@ hipError_t run_pair_pass(const Plan& pl, int stage, PassArgs<T> a, hipStream_t s
     blocks = (unsigned)pl.nublocks;
     a.blist = pl.d_ublocks;
     if (blocks == 0) return hipSuccess;
+  }
+  if (a.dim3 && reg_pair_lines<T>(a.L) > 0 && 2 * a.nin == a.L && 2 * a.nout == a.L) {
+    hipError_t e = hipErrorInvalidValue;
+    stage_mark(pl, stage, 0, s);
+    if constexpr (sizeof(T) == 8) e = launch_reg_pair<T, MODE>(a, blocks, s);
+    stage_mark(pl, stage, 1, s);
+    return e;
   }
   const int gse = a.dim3 ? a.sym.gs0 : a.sym.gs1;
   const int ngte = (a.L + (1 << gse) - 1) >> gse;
@@ -668,6 +673,7 @@ std::vector<int> split_unmix_blocks(const Plan& pl, const std::vector<unsigned c
     b.L = a.L;
     b.A = a.A;
     b.B = a.B;
+    b.dim3 = a.dim3;
     nblocks = pair_geometry<float>(b);
     a.P = b.P;
     a.cb = b.cb;

@@ -1093,8 +1093,16 @@ Status build_plan(Plan& pl, const jgb_params* p) {
     pl.ntouched = (int)tl.size();
     TRY(dev_alloc(pl, &pl.d_touched, sizeof(int) * std::max<size_t>(tl.size(), 1)));
     if (!tl.empty()) TRY(upload(pl, pl.d_touched, tl.data(), sizeof(int) * tl.size()));
-    TRY(dev_alloc(pl, &pl.d_tflag, (size_t)pl.ngtiles));
-    TRY(upload(pl, pl.d_tflag, tf.data(), (size_t)pl.ngtiles));
+    {
+      // the tiles' flags, then those of the tile columns along the paired
+      // passes' axis (a0 in 3D, a1 in 2D)
+      std::vector<unsigned char> all(tf);
+      const int along = pl.gnt[pl.dim == 3 ? 0 : 1], ncol = pl.ngtiles / along;
+      all.resize(tf.size() + ncol, 0);
+      for (int t = 0; t < pl.ngtiles; ++t) all[tf.size() + t % ncol] |= tf[t];
+      TRY(dev_alloc(pl, &pl.d_tflag, all.size()));
+      TRY(upload(pl, pl.d_tflag, all.data(), all.size()));
+    }
     // the unmix pass's blocks: those whose line pairs cross a touched tile
     {
       std::vector<int> ub = split_unmix_blocks(pl, tf);

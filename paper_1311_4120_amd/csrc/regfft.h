@@ -289,14 +289,15 @@ __device__ __forceinline__ void xdft5(C2<float>* v) {
   v[2] = xadd_i<SG>(r2, q2);
   v[3] = xadd_i<-SG>(r2, q2);
 }
-template <int SG>
+template <int SG, bool PAD>
 __device__ __forceinline__ void xdft16(C2<float>* v) {
   constexpr float c1 = (float)Root<1, 16>::c, s1 = (float)Root<1, 16>::s, r = (float)Root<1, 8>::c, s = (float)SG;
   C2<float> a[4][4];  // a[n2][k1]
 #pragma unroll
   for (int n2 = 0; n2 < 4; ++n2) {
     C2<float> t[4] = {v[n2], v[4 + n2], v[8 + n2], v[12 + n2]};
-    xdft4<SG>(t);
+    if constexpr (PAD) xdft4_pad<SG>(t);
+    else xdft4<SG>(t);
 #pragma unroll
     for (int k1 = 0; k1 < 4; ++k1) a[n2][k1] = t[k1];
   }
@@ -320,7 +321,7 @@ __device__ __forceinline__ void xdft16(C2<float>* v) {
 }
 template <int SG, int R, bool PAD>
 __device__ __forceinline__ void xdft(C2<float>* v) {
-  static_assert(!PAD || R == 4 || R == 8, "padded radix");
+  static_assert(!PAD || R == 4 || R == 8 || R == 16, "padded radix");
   if constexpr (R == 2) {
     const C2<float> a = v[0], b = v[1];
     v[0] = C2<float>{a.x + b.x, a.y + b.y};
@@ -331,7 +332,7 @@ __device__ __forceinline__ void xdft(C2<float>* v) {
   if constexpr (R == 4 && !PAD) xdft4<SG>(v);
   if constexpr (R == 5) xdft5<SG>(v);
   if constexpr (R == 8) xdft8<SG, PAD>(v);
-  if constexpr (R == 16) xdft16<SG>(v);
+  if constexpr (R == 16) xdft16<SG, PAD>(v);
 }
 
 #pragma clang fp contract(fast)
@@ -390,16 +391,18 @@ struct RegShape : SEQ {
   using SEQ::L;
   using SEQ::TPL;
   static constexpr int V = STR && sizeof(T) == 4 ? 2 : 1;
-  // the exchange moves the real and then the imaginary parts in float64: half
-  // the LDS, so twice the blocks per CU (45.3 against 47.2 us for the first
-  // inverse pass at 128^3; no gain in float32)
-  static constexpr bool SPLIT = sizeof(T) == 8;
-  static constexpr int es = SPLIT ? sizeof(T) : 2 * V * (int)sizeof(T);  // bytes of an LDS element
+  // the exchange moves the real and then the imaginary parts: half the LDS, so
+  // twice the blocks per CU (45.3 against 47.2 us for the first inverse pass of
+  // a 128^3 grid in float64)
+  static constexpr int es = V * (int)sizeof(T);  // bytes of an LDS element
   static constexpr int R1 = SEQ::radix(0);
-  static constexpr int pitch = STR ? L : L + L / R1;  // contiguous passes: one pad per R1 elements
+  // LDS rows of a line: one pad per R1 elements, so that the elements that
+  // consecutive butterflies write together (R1 apart) fall on different banks,
+  // at a constant stride per output
+  static constexpr int pitch = L + L / R1;
   static constexpr int str_lines() {
     int lb = 256 / (2 * V * (int)sizeof(T));
-    while (lb * L * es > 65536 || lb * TPL > 512) lb /= 2;
+    while (lb * pitch * es > 65536 || lb * TPL > 512) lb /= 2;
     return lb;
   }
   static constexpr int LB = STR ? str_lines() : (TPL >= 256 ? 1 : 256 / TPL);  // line groups of V
@@ -407,18 +410,9 @@ struct RegShape : SEQ {
   static constexpr bool wave_sync = !STR && 64 % TPL == 0;  // a line never leaves its wavefront
   static constexpr size_t lds = (size_t)LB * pitch * es < NT * sizeof(double) ? NT * sizeof(double) : (size_t)LB * pitch * es;
   static_assert(NT <= 1024 && lds <= 65536, "pass shape");
-  // LDS element of element e of line group l.  Strided: rows of LB elements;
-  // the low bits of e are flipped with e / R1 so that the rows that consecutive
-  // butterflies write together (R1 apart) fall on different banks.
-  static __device__ __forceinline__ int at(int l, int e) {
-    if constexpr (STR) {
-      constexpr int row = LB * es;
-      constexpr int rb = row >= 256 ? 1 : 256 / row;  // rows per pass over the banks
-      return ((e ^ ((e / R1) & (rb < 4 ? rb - 1 : 3))) * LB) + l;
-    } else {
-      return l * pitch + e + e / R1;
-    }
-  }
+  // LDS elements between two rows, and the first of line group l
+  static constexpr int row = STR ? LB : 1;
+  static __device__ __forceinline__ int line_base(int l) { return STR ? l : l * pitch; }
 };
 
 // V neighbouring complex values, one access.
@@ -438,42 +432,68 @@ __device__ __forceinline__ void reg_sync() {
   }
 }
 
-// Exchange through LDS: every thread writes v[.][0 .. NW - 1] at wi(r) and reads
-// v[.][0 .. NR - 1] from ri(r).
-template <typename T, typename S, int NW, int NR, typename WI, typename RI>
-__device__ __forceinline__ void reg_exchange(void* smem, C2<T> (&v)[S::V][S::NV], WI wi, RI ri) {
-  constexpr bool WAVE = S::wave_sync;
-  if constexpr (S::SPLIT) {
-    static_assert(S::V == 1, "split exchanges move one line per thread");
-    T* s = reinterpret_cast<T*>(smem);
+// V values of one part (real or imaginary), one LDS access.
+template <typename T, int V>
+struct alignas(V * sizeof(T)) PV {
+  T u[V];
+};
+
+// The first row of butterfly q's outputs of stage s, and the rows between two
+// of them; likewise of its inputs.
+template <typename SEQ, int s>
+__device__ __forceinline__ int out_row(int q) {
+  constexpr int R1 = SEQ::radix(0), R = SEQ::radix(s), NS = SEQ::ns(s);
+  if constexpr (s == 0) return q * (R1 + 1);
+  const int k = q % NS, e = (q - k) * R + k;
+  return e + e / R1;
+}
+template <typename SEQ, int s>
+constexpr int out_step() { return s == 0 ? 1 : SEQ::ns(s) + SEQ::ns(s) / SEQ::radix(0); }
+template <typename SEQ, int s>
+__device__ __forceinline__ int in_row(int q) { return q + q / SEQ::radix(0); }
+template <typename SEQ, int s>
+constexpr int in_step() {
+  constexpr int n = SEQ::L / SEQ::radix(s);
+  static_assert(n % SEQ::radix(0) == 0, "a later stage's inputs are a multiple of R1 apart");
+  return n + n / SEQ::radix(0);
+}
+
+// Exchange through LDS from stage s - 1's outputs in v to stage s's inputs: the
+// real parts, then the imaginary ones.
+template <typename T, typename S, int s>
+__device__ __forceinline__ void reg_exchange(void* smem, C2<T> (&v)[S::V][S::NV], int l, int j) {
+  constexpr int V = S::V, P = S::radix(s - 1), NW = S::nb(s - 1), R = S::radix(s), NR = S::nb(s), row = S::row;
+  constexpr int os = out_step<S, s - 1>(), is = in_step<S, s>();
+  typedef PV<T, V> E;
+  E* const m = reinterpret_cast<E*>(smem) + S::line_base(l);
+  T re[V][NR * R];
 #pragma unroll
-    for (int r = 0; r < NW; ++r) s[wi(r)] = v[0][r].x;
-    reg_sync<WAVE>();
-    T re[NR];
+  for (int part = 0; part < 2; ++part) {
+    if (part || s > 1) reg_sync<S::wave_sync>();  // what was there has been read
 #pragma unroll
-    for (int r = 0; r < NR; ++r) re[r] = s[ri(r)];
-    reg_sync<WAVE>();
+    for (int i = 0; i < NW; ++i) {
+      E* const w = m + row * out_row<S, s - 1>(S::template bf<s - 1>(j, i));
 #pragma unroll
-    for (int r = 0; r < NW; ++r) s[wi(r)] = v[0][r].y;
-    reg_sync<WAVE>();
+      for (int r = 0; r < P; ++r) {
+        E x;
 #pragma unroll
-    for (int r = 0; r < NR; ++r) v[0][r] = C2<T>{re[r], s[ri(r)]};
-  } else {
-    typedef CV<T, S::V> E;
-    E* s = reinterpret_cast<E*>(smem);
-#pragma unroll
-    for (int r = 0; r < NW; ++r) {
-      E x;
-#pragma unroll
-      for (int u = 0; u < S::V; ++u) x.u[u] = v[u][r];
-      s[wi(r)] = x;
+        for (int u = 0; u < V; ++u) x.u[u] = part ? v[u][i * P + r].y : v[u][i * P + r].x;
+        w[r * os * row] = x;
+      }
     }
-    reg_sync<WAVE>();
+    reg_sync<S::wave_sync>();
 #pragma unroll
-    for (int r = 0; r < NR; ++r) {
-      const E x = s[ri(r)];
+    for (int i = 0; i < NR; ++i) {
+      const E* const q = m + row * in_row<S, s>(S::template bf<s>(j, i));
 #pragma unroll
-      for (int u = 0; u < S::V; ++u) v[u][r] = x.u[u];
+      for (int r = 0; r < R; ++r) {
+        const E x = q[r * is * row];
+#pragma unroll
+        for (int u = 0; u < V; ++u) {
+          if (part == 0) re[u][i * R + r] = x.u[u];
+          else v[u][i * R + r] = C2<T>{re[u][i * R + r], x.u[u]};
+        }
+      }
     }
   }
 }
@@ -493,29 +513,29 @@ __device__ __forceinline__ void reg_butterfly(C2<T>* v) {
   }
 }
 
+// Table entry t by a 32-bit byte offset from the table's base (the base stays in
+// scalar registers).
+template <typename T>
+__device__ __forceinline__ C2<T> table_at(const C2<T>* __restrict__ tw, int t) {
+  return *reinterpret_cast<const C2<T>*>(reinterpret_cast<const char*>(tw) + (uint32_t)t * (uint32_t)sizeof(C2<T>));
+}
+
 // Stages s .. NS - 1, from stage s - 1's outputs in v to the last stage's
 // (butterfly i's output r at v[i RL + r]).
 template <typename T, typename S, int SG, int s>
 __device__ __forceinline__ void reg_stages(void* smem, C2<T> (&v)[S::V][S::NV], int l, int j,
                                            const C2<T>* __restrict__ tw) {
   if constexpr (s < S::NS) {
-    constexpr int L = S::L, P = S::radix(s - 1), NP = S::ns(s - 1), R = S::radix(s), NS = S::ns(s);
+    constexpr int L = S::L, R = S::radix(s), NS = S::ns(s);
     constexpr int NB = S::nb(s);
-    if constexpr (s > 1) reg_sync<S::wave_sync>();  // the exchange before has been read
-    reg_exchange<T, S, S::nb(s - 1) * P, NB * R>(
-        smem, v,
-        [&](int r) {
-          const int q = S::template bf<s - 1>(j, r / P), k = q % NP;
-          return S::at(l, (q - k) * P + k + (r % P) * NP);
-        },
-        [&](int r) { return S::at(l, S::template bf<s>(j, r / R) + (r % R) * (L / R)); });
+    reg_exchange<T, S, s>(smem, v, l, j);
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
       const int k = S::template bf<s>(j, i) % NS;
 #pragma unroll
       for (int r = 1; r < R; ++r) {
         // w_(Ns R)^(r k); the table holds exp(-2 pi i t / L)
-        C2<T> w = tw[r * k * (L / (NS * R))];
+        C2<T> w = table_at(tw, r * k * (L / (NS * R)));
         if constexpr (SG > 0) w.y = -w.y;
 #pragma unroll
         for (int u = 0; u < S::V; ++u) {

@@ -133,6 +133,7 @@ SplitSym make_split_sym(const Plan& pl) {
     off += 2 * pl.nf[i];
   }
   a.tflag = pl.d_tflag;
+  a.tcol = pl.d_tflag ? pl.d_tflag + pl.ngtiles : nullptr;
   return a;
 }
 

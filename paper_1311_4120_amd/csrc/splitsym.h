@@ -30,6 +30,7 @@ struct SplitSym {
   const double* kt;    // per axis: k_a(q) for q < nf_a, then exp(-k_a(q)^2 / a)
   int koff[3], eoff[3];
   const unsigned char* tflag;  // per gather tile: 1 if some node touches it
+  const unsigned char* tcol;   // per column of gather tiles along the paired passes' axis: 1 if one of its tiles is touched
 };
 
 // Host: the plan's symbol parameters (split.hip).
@@ -46,13 +47,15 @@ __device__ inline int split_mirror(int q, int nf) { return q ? nf - q : 0; }
 // of per-axis tables, so 1 - p is 1 minus that product: at the grid's smallest
 // nonzero |k| the subtraction costs under four bits at the default scale
 // a = 2 dk^2.
-__device__ inline double split_symbol_core(const SplitSym& s, double kk, double wprod, double nk, double mk) {
+__device__ inline double split_symbol_core3(const SplitSym& s, double kk, double wprod, double nk, double mk) {
   if (kk == 0.0) return s.kernel == JGB_COULOMB_3D ? s.inv_vol / s.a : 0.0;
-  if (s.dim == 3) {
-    const double omp = 1.0 - wprod;
-    if (s.kernel == JGB_COULOMB_3D) return s.inv_vol * omp / kk;
-    return s.inv_vol * omp * (3.0 * nk * mk / kk - s.mn);
-  }
+  const double omp = 1.0 - wprod;
+  if (s.kernel == JGB_COULOMB_3D) return s.inv_vol * omp / kk;
+  return s.inv_vol * omp * (3.0 * nk * mk / kk - s.mn);
+}
+__device__ inline double split_symbol_core(const SplitSym& s, double kk, double wprod, double nk, double mk) {
+  if (s.dim == 3) return split_symbol_core3(s, kk, wprod, nk, mk);
+  if (kk == 0.0) return 0.0;
   const double kabs = sqrt(kk);
   const double omp = 0.5 * erfc(-12.0 * (kabs - 0.5 * (s.r0 + s.r1)) / (s.r1 - s.r0));
   if (s.kernel == JGB_COULOMB_2D) return s.inv_vol * omp / kabs;
