@@ -27,6 +27,12 @@ constexpr size_t kInterpLdsCap = 144 * 1024;
 constexpr int kMaxLine = 1024;
 // Output tile of the type-1 gather kernel: TX x TY lanes, TZ points per lane.
 constexpr int kTileZ = 16;
+// Wavefronts (work items) of a block of the interpolation by tiles.
+constexpr int kTileWaves = 4;
+// List entries of such an item at most (a multiple of 16).  128^3, all nodes,
+// float64 and float32: 271 and 62 us at 192, 267 and 61 at 384, 270 and 61 at
+// 512 (fewer items cost fewer starts, more balance the device better).
+constexpr int kTileItem = 384;
 // Output tile of the type-1 gather along axis 2 (the bins above stay kTileZ).
 constexpr int kGatherZ = 8;
 // Offset added to the signed tile-relative footprint starts of the gather lists
@@ -85,6 +91,15 @@ struct WorkItem {
   int vbegin;  // range of the node list d_list handled by this item
   int vend;
   int slot;    // -1: write the tile to the grid; >= 0: write partial slot
+};
+
+// A work item of the interpolation by tiles: one wavefront's run of a tile's
+// list.
+struct TileItem {
+  uint16_t t0, t1, t2;  // the tile's coordinates
+  uint16_t count;       // list entries (0: idle slot of the dispatch order)
+  int begin;            // first one in d_tlist
+  int group;            // their first place in d_tneed
 };
 
 // A work item of the spreading by rings: a tile (slot -1) or one of its
@@ -185,7 +200,13 @@ struct Plan {
   // kernel sums each node's partials in a fixed order through the node-major
   // index d_nstart / d_npos (node j's entries are d_npos[d_nstart[j] ..
   // d_nstart[j + 1])).
+  // The work items are per wavefront, 8 kTileWaves of them to eight blocks.
   bool tile_ok = false;        // the tables below are built (autotuned 3D plans)
+  int2* d_tlist = nullptr;     // the gather's lists, each tile's entries ordered by footprint
+  int* d_tneed = nullptr;      // per 16 consecutive entries of a tile: bit x + 8 h if the footprint of one
+                               // of them reaches the tile's points (x, y = 4h .. 4h + 3)
+  TileItem* d_titems = nullptr;
+  int ntitems = 0;
   bool tile_interp = false;    // and the interpolation uses them
 
   // Spreading by rings (3D): the nodes of one ring (r_a, theta_b) share their

@@ -318,6 +318,21 @@ __global__ void __launch_bounds__(kInterpThreads) k_interp_b(const InterpArgs<T>
 // B[k][j], so lane j + 16k holds node j's kernel values; the result register
 // r of lane l holds D[row(l, r)][l mod 16], column l mod 16 being the lane's
 // own node, so the weighting by phi_2 needs no exchange between lanes.
+//
+// One wavefront takes one work item: lists are short (a median of 200 entries
+// at 128^3), and four wavefronts sharing one each paid the start.  The list is
+// ordered so that the 16 nodes of a group reach the same points (order_tiles),
+// and the products that none of them reaches, known from the plan, are
+// skipped: 9.2 of 16 products a group instead of 11.8 at 12 taps.  A node's
+// values lie between zeros in LDS, so a lane reads its taps at one address and
+// constant offsets.  No load in the loop is conditional and the store of a
+// group waits for the next one's loads: otherwise the compiler waits for a
+// load where a condition ends, or for the store, and the loads a group ahead
+// hide nothing.  128^3, 1 048 576 nodes: float64 322 us -> 267, float32 91 ->
+// 61; 256^3, 8 388 608 nodes, float32 660 -> 494.  What bounds it (float64):
+// 1.5 GB of records that miss L2 (each is read for 12 tiles) at 5.7 TB/s; with
+// the records in cache 210 us, without the products 237, without both 166 (the
+// LDS copies and taps).
 
 typedef double d4v __attribute__((ext_vector_type(4)));
 typedef float f4v __attribute__((ext_vector_type(4)));
@@ -330,7 +345,26 @@ struct TileMfma<double> {
   static __device__ __forceinline__ acc_t mma(double a, double b, acc_t c) {
     return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
   }
-  static __device__ __forceinline__ int row(int l, int r) { return 4 * r + (l >> 4); }
+  static __device__ __forceinline__ constexpr int row(int l, int r) { return 4 * r + (l >> 4); }
+  // Sum over z of a column of D weighted by its node's phi_2: result registers
+  // 0 and 1 hold re, 2 and 3 im, the lane's four rows of 16 the other z.  The
+  // rows exchange by swapping half registers: first re and im between odd and
+  // even rows, then the halves of the wavefront; re ends up in row 0, im in
+  // row kImRow.
+  static constexpr int kImRow = 1;
+  static __device__ __forceinline__ double zsum(const acc_t& d, const double (&pz)[4]) {
+    double re = 0.0, im = 0.0;
+    re += d[0] * pz[0];
+    re += d[1] * pz[1];
+    im += d[2] * pz[2];
+    im += d[3] * pz[3];
+    const auto l = __builtin_amdgcn_permlane16_swap(__double2loint(re), __double2loint(im), false, false);
+    const auto h = __builtin_amdgcn_permlane16_swap(__double2hiint(re), __double2hiint(im), false, false);
+    const double s = __hiloint2double(h[0], l[0]) + __hiloint2double(h[1], l[1]);
+    const auto l2 = __builtin_amdgcn_permlane32_swap(__double2loint(s), __double2loint(s), false, false);
+    const auto h2 = __builtin_amdgcn_permlane32_swap(__double2hiint(s), __double2hiint(s), false, false);
+    return __hiloint2double(h2[0], l2[0]) + __hiloint2double(h2[1], l2[1]);
+  }
 };
 template <>
 struct TileMfma<float> {
@@ -338,18 +372,34 @@ struct TileMfma<float> {
   static __device__ __forceinline__ acc_t mma(float a, float b, acc_t c) {
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
   }
-  static __device__ __forceinline__ int row(int l, int r) { return 4 * (l >> 4) + r; }
+  static __device__ __forceinline__ constexpr int row(int l, int r) { return 4 * (l >> 4) + r; }
+  // as above: rows 0 and 1 hold re of z = 0..3 and 4..7, rows 2 and 3 im
+  static constexpr int kImRow = 2;
+  static __device__ __forceinline__ float zsum(const acc_t& d, const float (&pz)[4]) {
+    float v = 0.f;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) v += d[r] * pz[r];
+    const auto s = __builtin_amdgcn_permlane16_swap(__float_as_int(v), __float_as_int(v), false, false);
+    return __int_as_float(s[0]) + __int_as_float(s[1]);
+  }
 };
+
+// Zeros before, between and after the axes' values of a record's LDS copy: a
+// tap index of an 8-point tile side runs from -7 to W + 6.
+constexpr int kTapPad = 7;
+// LDS values of a wavefront's 16 copies, each followed by kTapPad zeros of the
+// next (the last one's own)
+__host__ __device__ constexpr int tile_lds_values(int lstride) { return 16 * lstride + kTapPad; }
 
 template <typename T>
 struct TileArgs {
   int nf0, nf1, nf2;
   int w0, w1, w2;
-  int nt1, nt2;
   int width, rstride;
   int lstride;        // values between the LDS copies of two records (>= rstride; see the launcher)
   const int2* list;
-  const WorkItem* items;
+  const TileItem* items;
+  const int* need;    // per 16 entries of a tile, the products its nodes reach
   const T* F;         // oversampled grid, interleaved (re, im), rows of hs2 along axis 2
   int hs2;            // row stride of F along axis 2
   int r2c;            // F holds q2 = 0 .. nf2/2 only: F(q) = conj F(-q) beyond
@@ -362,7 +412,6 @@ __device__ __forceinline__ V tload(const void* base, uint32_t byte_off) {
   return *reinterpret_cast<const V*>(reinterpret_cast<const char*>(base) + byte_off);
 }
 
-constexpr int kTileWaves = 4;
 
 // NF: 16-byte pieces of a record each lane fetches, ceil(record pieces / 4).
 template <typename T, bool NOWRAP, int NF>
@@ -372,14 +421,12 @@ __device__ __forceinline__ void interp_tile_body(const TileArgs<T>& a, const int
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   // the wave's copies of its group's 16 node records
-  T* recs = reinterpret_cast<T*>(smem_raw) + (size_t)wave * 16 * a.lstride;
-  const WorkItem item = a.items[blk];
-  if (item.tile < 0) return;  // idle slot of the dispatch order
-  const int tile = item.tile;
-  const int t2 = tile % a.nt2;
-  const int t1 = (tile / a.nt2) % a.nt1;
-  const int t0 = tile / (a.nt2 * a.nt1);
-  const int o0 = t0 * 8, o1 = t1 * 8, o2 = t2 * 8;
+  T* recs = reinterpret_cast<T*>(smem_raw) + (size_t)wave * tile_lds_values(a.lstride);
+  // the wave's own work item: eight blocks (one per XCD) take 32 consecutive
+  // places of the dispatch order, place p on XCD p mod 8
+  const TileItem item = a.items[(blk >> 3) * (8 * kTileWaves) + 8 * wave + (blk & 7)];
+  if (item.count == 0) return;
+  const int o0 = 8 * item.t0, o1 = 8 * item.t1, o2 = 8 * item.t2;
   const int j16 = lane & 15, k4 = lane >> 4;
 
   // B: the tile's grid values, product t covering points m = 4t .. 4t + 3
@@ -387,112 +434,148 @@ __device__ __forceinline__ void interp_tile_body(const TileArgs<T>& a, const int
   // points off the grid read zero
   T B[16];
   {
-    const int z = j16 & 7, part = j16 >> 3;
+    const int z = j16 & 7, part = j16 >> 3, gz = o2 + z;
+    // the Hermitian half: the other half is the conjugate mirror image
+    const bool mirror = a.r2c && 2 * gz > a.nf2;
+    const bool inz = gz < a.nf2;
+    const int fz = !inz ? 0 : mirror ? a.nf2 - gz : gz;
+    const int64_t plane = (int64_t)a.nf1 * a.hs2;
+    const T* row[2];  // of the plane gx = o0
+    bool iny[2];
+    const int fx = (mirror && o0) ? a.nf0 - o0 : o0;
 #pragma unroll
-    for (int t = 0; t < 16; ++t) {
-      int gx = o0 + (t >> 1), gy = o1 + ((t & 1) << 2) + k4, gz = o2 + z;
-      const bool in = gx < a.nf0 && gy < a.nf1 && gz < a.nf2;
-      // the Hermitian half: the other half is the conjugate mirror image
-      const bool mirror = a.r2c && 2 * gz > a.nf2;
-      if (mirror) {
-        gx = gx ? a.nf0 - gx : 0;
-        gy = gy ? a.nf1 - gy : 0;
-        gz = a.nf2 - gz;
-      }
-      const T v = in ? a.F[2 * (((int64_t)gx * a.nf1 + gy) * a.hs2 + gz) + part] : T(0);
-      B[t] = (mirror && part) ? -v : v;
+    for (int h = 0; h < 2; ++h) {
+      const int gy = o1 + 4 * h + k4;
+      iny[h] = inz && gy < a.nf1;
+      const int fy = !iny[h] ? 0 : (mirror && gy) ? a.nf1 - gy : gy;
+      row[h] = a.F + 2 * (fx * plane + (int64_t)fy * a.hs2 + fz) + part;
+    }
+    // from plane to plane: down the mirror image, whose plane 0 wraps to nf0
+    const int64_t step = mirror ? -2 * plane : 2 * plane;
+    const int64_t wrap = (mirror && o0 == 0) ? 2 * plane * a.nf0 : 0;
+    const int xend = min(8, a.nf0 - o0);
+    int64_t off = 0;
+#pragma unroll
+    for (int x = 0; x < 8; ++x) {
+      B[2 * x] = row[0][off];
+      B[2 * x + 1] = row[1][off];
+      if (x + 1 < xend) off += x == 0 ? step + wrap : step;
+    }
+    if (mirror && part) {
+#pragma unroll
+      for (int t = 0; t < 16; ++t) B[t] = -B[t];
+    }
+    if (xend < 8 || o1 + 8 > a.nf1 || o2 + 8 > a.nf2) {
+#pragma unroll
+      for (int t = 0; t < 16; ++t)
+        if (!iny[t & 1] || (t >> 1) >= xend) B[t] = T(0);
     }
   }
-  // the tile z and part of the lane's result registers
-  int zr[4], pr[4];
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int row = TileMfma<T>::row(lane, r);
-    zr[r] = row & 7;
-    pr[r] = row >> 3;
-  }
-
   constexpr int bias = NOWRAP ? kGatherBias : 0;
-  constexpr int kChunk = 16 / sizeof(T);  // values per 16-byte copy
+  constexpr int kChunk = 16 / sizeof(T);  // values per 16-byte piece
   const int W = a.width;
   const int nchunk = a.rstride / kChunk;  // 16-byte pieces of a record
   const uint32_t rbytes = (uint32_t)(a.rstride * sizeof(T));
-  const T* myrec = recs + j16 * a.lstride;
-  const int vb = item.vbegin, ve = item.vend;
+  // the records' LDS copies: each axis's values between kTapPad zeros, so that
+  // the taps of a tile side are consecutive values wherever the footprint lies
+  // (the zeros are written once; the last ones of a copy are the first of the
+  // next)
+  const int astride = W + kTapPad;
+  T* myrec = recs + j16 * a.lstride;
+  for (int c = lane; c < tile_lds_values(a.lstride); c += 64) recs[c] = T(0);
+  // where the values of the lane's pieces go
+  int dst[NF * kChunk];
+  uint32_t src[NF];
+#pragma unroll
+  for (int m = 0; m < NF; ++m) {
+    const int c = min(k4 + 4 * m, nchunk - 1);  // a lane without a piece m copies the last once more
+    src[m] = (uint32_t)c * 16u;
+#pragma unroll
+    for (int i = 0; i < kChunk; ++i) {
+      const int e = c * kChunk + i, axis = (e > W) + (e > 2 * W + 1), off = e - axis * (W + 1);
+      dst[m * kChunk + i] = kTapPad + axis * astride + off;  // off >= W: a zero of the record onto a zero
+    }
+  }
+  // the item's products, one group of 16 entries a lane: bit x + 8 h for the
+  // tile's points (x, y = 4h .. 4h + 3)
+  static_assert(kTileItem <= 64 * 16, "an item's groups have a lane each");
+  const int vb = item.begin, ve = vb + item.count;
+  const int needs = a.need[item.group + min(lane, (item.count - 1) >> 4)];
+  // LDS byte offsets of tap 0 at footprint start 0 (starts carry the bias)
+  int bx = (int)(((size_t)(myrec - reinterpret_cast<T*>(smem_raw)) + kTapPad + bias) * sizeof(T));
+  int by = bx + (int)((astride + k4) * sizeof(T)), bz = bx + (int)((2 * astride + (TileMfma<T>::row(lane, 0) & 7)) * sizeof(T));
+  asm volatile("" : "+v"(bx), "+v"(by), "+v"(bz));
   // node j16's record reaches the wave's LDS through registers, one group
   // ahead: the four lanes of the node take every fourth 16-byte piece
   // (coalesced runs instead of one scattered load per kernel value) while the
   // group before is computed; the list entries come one group further ahead
   uint4 pre[NF];
-  int g0 = vb + 16 * wave;
-  int2 entc = tload<int2>(a.list, (uint32_t)min(g0 + j16, ve - 1) * 8u);
-#define JGB_TILE_FETCH()                                                                                     \
-  do {                                                                                                       \
-    const uint32_t rec_ = (uint32_t)entc.x * rbytes;                                                         \
-    _Pragma("unroll") for (int m = 0; m < NF; ++m) {                                                         \
-      const int c = k4 + 4 * m;                                                                              \
-      pre[m] = c < nchunk ? tload<uint4>(a.wts, rec_ + (uint32_t)c * 16u) : uint4{0u, 0u, 0u, 0u};           \
-    }                                                                                                        \
-  } while (0)
-  if (g0 < ve) JGB_TILE_FETCH();
-  int2 entn = tload<int2>(a.list, (uint32_t)min(g0 + 16 * kTileWaves + j16, ve - 1) * 8u);
-  for (; g0 < ve; g0 += 16 * kTileWaves) {
-    const int idx = g0 + j16;
-    const bool valid = idx < ve;
-    const int2 ent = entc;
-    const int ex = ent.y & 1023, ey = (ent.y >> 10) & 1023, ez = (ent.y >> 20) & 1023;
+  int g0 = vb;
+  auto entry = [&](int g) { return tload<int2>(a.list, (uint32_t)min(g + j16, ve - 1) * 8u); };
+  auto fetch = [&](int node) {
+    const uint32_t rec = (uint32_t)node * rbytes;
+#pragma unroll
+    for (int m = 0; m < NF; ++m) pre[m] = tload<uint4>(a.wts, rec + src[m]);
+  };
+  int2 entc = entry(g0), entn = entry(g0 + 16);
+  fetch(entc.x);
+  // the group before, stored when the next loads go out: re in the lanes of
+  // row 0, im in row kImRow
+  T sum = T(0);
+  T* const out = reinterpret_cast<T*>(a.ipart) + (k4 == 0 ? 0 : 1);
+  const bool keeps = k4 == 0 || k4 == TileMfma<T>::kImRow;
+  for (; g0 < ve; g0 += 16) {
+    const int ex = entc.y & 1023, ey = (entc.y >> 10) & 1023, ez = (entc.y >> 20) & 1023;
     __builtin_amdgcn_wave_barrier();  // the previous group's reads are done
 #pragma unroll
     for (int m = 0; m < NF; ++m) {
-      const int c = k4 + 4 * m;
-      if (c < nchunk) *reinterpret_cast<uint4*>(recs + j16 * a.lstride + c * kChunk) = pre[m];
+      T v[kChunk];
+      __builtin_memcpy(v, &pre[m], 16);
+#pragma unroll
+      for (int i = 0; i < kChunk; ++i) myrec[dst[m * kChunk + i]] = v[i];
     }
     __builtin_amdgcn_wave_barrier();
-    if (g0 + 16 * kTileWaves < ve) {
-      entc = entn;
-      JGB_TILE_FETCH();
-      entn = tload<int2>(a.list, (uint32_t)min(g0 + 32 * kTileWaves + j16, ve - 1) * 8u);
-    }
+    // ahead of the loads, so that the wait for them next time has no younger
+    // store to wait for
+    if (keeps && g0 > vb) out[2 * (int64_t)(g0 - 16 + j16)] = sum;
+    fetch(entn.x);  // past the end of the list: the last entry's once more
+    entc.y = entn.y;
+    entn = entry(g0 + 32);
     // node j16's kernel values at the tile's 8 x, the lane's 2 y and the z of
-    // its result registers; taps outside the footprint read the zero after
-    // their axis's values (a lane past the end of the list computes from a
+    // its result registers (a lane past the end of the list computes from a
     // copy of the last entry and stores nothing)
-    auto tap = [&](int d, int axis_nf, int axis) {
-      if (!NOWRAP && d < 0) d += axis_nf;
-      return myrec[axis * (W + 1) + (int)min((uint32_t)d, (uint32_t)W)];
-    };
     T px[8], py[2], pz[4];
+    if (NOWRAP) {
+      auto taps = [&](int b, int e) { return reinterpret_cast<const T*>(smem_raw + (b - e * (int)sizeof(T))); };
+      const T *tx = taps(bx, ex), *ty = taps(by, ey), *tz = taps(bz, ez);
 #pragma unroll
-    for (int x = 0; x < 8; ++x) px[x] = tap(x + bias - ex, a.nf0, 0);
+      for (int x = 0; x < 8; ++x) px[x] = tx[x];
+      py[0] = ty[0];
+      py[1] = ty[4];
 #pragma unroll
-    for (int h = 0; h < 2; ++h) py[h] = tap(k4 + 4 * h + bias - ey, a.nf1, 1);
+      for (int r = 0; r < 4; ++r) pz[r] = tz[TileMfma<T>::row(0, r) & 7];
+    } else {
+      auto tap = [&](int d, int axis_nf, int axis) {
+        if (d < 0) d += axis_nf;
+        return myrec[kTapPad + axis * astride + (int)min((uint32_t)d, (uint32_t)W)];
+      };
 #pragma unroll
-    for (int r = 0; r < 4; ++r) pz[r] = tap(zr[r] + bias - ez, a.nf2, 2);
+      for (int x = 0; x < 8; ++x) px[x] = tap(x - ex, a.nf0, 0);
+#pragma unroll
+      for (int h = 0; h < 2; ++h) py[h] = tap(k4 + 4 * h - ey, a.nf1, 1);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) pz[r] = tap((TileMfma<T>::row(lane, r) & 7) - ez, a.nf2, 2);
+    }
+    // the products no node of the group reaches would add exact zeros
+    const int need = __builtin_amdgcn_readlane(needs, (g0 - vb) >> 4);
     acc_t acc = acc_t{T(0), T(0), T(0), T(0)};
-    // product t covers the tile points (x = t/2, y = 4 (t mod 2) + 0..3); it
-    // is skipped when none of the 16 nodes' footprints reaches them (it would
-    // add exact zeros)
 #pragma unroll
     for (int t = 0; t < 16; ++t) {
-      const T pa = px[t >> 1] * py[t & 1];
-      if (__ballot(pa != T(0))) acc = TileMfma<T>::mma(B[t], pa, acc);
+      if (need & (1 << ((t >> 1) + 8 * (t & 1)))) acc = TileMfma<T>::mma(B[t], px[t >> 1] * py[t & 1], acc);
     }
-    T re = T(0), im = T(0);
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      if (pr[r] == 0)
-        re += acc[r] * pz[r];
-      else
-        im += acc[r] * pz[r];
-    }
-    // the other three lane rows hold the node's other z
-    re += __shfl_xor(re, 16, 64);
-    im += __shfl_xor(im, 16, 64);
-    re += __shfl_xor(re, 32, 64);
-    im += __shfl_xor(im, 32, 64);
-    if (k4 == 0 && valid) a.ipart[idx] = C2<T>{re, im};
+    sum = TileMfma<T>::zsum(acc, pz);
   }
-#undef JGB_TILE_FETCH
+  if (keeps && g0 - 16 + j16 < ve) out[2 * (int64_t)(g0 - 16 + j16)] = sum;
 }
 
 template <typename T, bool NOWRAP, int NF>
@@ -633,23 +716,11 @@ hipError_t allow_lds(size_t smem) {
 }  // namespace
 
 // Values between the LDS copies of two node records in k_interp_tile: the
-// record length rounded so that copies stay 16-byte aligned, plus whole
-// 16-byte steps until the 16 copies of a wave start in 16 distinct pairs of
-// 4-byte banks (the lanes of one read touch one value of each copy).
+// three axes' values and their zeros, rounded up to an odd number so that the
+// 16 copies of a wave start in distinct 4-byte banks (pairs in float64).
 template <typename T>
-int tile_lds_stride(int rstride) {
-  const int step = 16 / (int)sizeof(T);
-  for (int s = rstride; s < rstride + 16 * step; s += step) {
-    bool ok = true;
-    for (int i = 0; i < 16 && ok; ++i)
-      for (int k = 0; k < i && ok; ++k) {
-        const int bi = (i * s * (int)sizeof(T) / 4) % 64, bk = (k * s * (int)sizeof(T) / 4) % 64;
-        const int span = (int)sizeof(T) / 4;
-        ok = !(bi < bk + span && bk < bi + span);
-      }
-    if (ok) return s;
-  }
-  return rstride;
+int tile_lds_stride(int width) {
+  return (3 * width + 3 * kTapPad) | 1;
 }
 
 // lanes per node of the reduction: four from ten list entries per node on
@@ -678,13 +749,12 @@ hipError_t launch_interp_tiles(const Plan& pl, InterpMode mode, void* out, hipSt
   a.w0 = pl.w[0];
   a.w1 = pl.w[1];
   a.w2 = pl.w[2];
-  a.nt1 = pl.gnt[1];
-  a.nt2 = pl.gnt[2];
   a.width = pl.width;
   a.rstride = record_stride(pl.width);
-  a.lstride = tile_lds_stride<T>(a.rstride);
-  a.list = pl.d_list;
-  a.items = pl.d_items;
+  a.lstride = tile_lds_stride<T>(a.width);
+  a.list = pl.d_tlist;
+  a.items = pl.d_titems;
+  a.need = pl.d_tneed;
   // Algorithm 2: the type-2 spectrum was separated into G's touched tiles
   a.F = (const T*)(pl.split ? pl.d_G : pl.d_F);
   a.hs2 = pl.split ? pl.nf[2] : pl.hs2;
@@ -692,10 +762,11 @@ hipError_t launch_interp_tiles(const Plan& pl, InterpMode mode, void* out, hipSt
   a.wts = (const T*)pl.nodes.wts;
   a.ipart = (C2<T>*)pl.d_ipart;
   stage_mark(pl, ST_INTERP, 0, s);
-  if (pl.nitems > 0) {
-    const size_t smem = (size_t)kTileWaves * 16 * a.lstride * sizeof(T);
-    const hipError_t e = pl.gather_nowrap ? launch_tile_kernel<T, true>(a, (unsigned)pl.nitems, smem, s)
-                                          : launch_tile_kernel<T, false>(a, (unsigned)pl.nitems, smem, s);
+  if (pl.ntitems > 0) {
+    const size_t smem = (size_t)kTileWaves * tile_lds_values(a.lstride) * sizeof(T);
+    const unsigned blocks = (unsigned)(pl.ntitems / kTileWaves);  // ntitems is a multiple of 8 kTileWaves
+    const hipError_t e = pl.gather_nowrap ? launch_tile_kernel<T, true>(a, blocks, smem, s)
+                                          : launch_tile_kernel<T, false>(a, blocks, smem, s);
     if (e != hipSuccess) return e;
   }
   stage_mark(pl, ST_INTERP, 1, s);

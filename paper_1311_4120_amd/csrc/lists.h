@@ -183,6 +183,62 @@ inline std::string gather_lists(const Geometry& g, bool nowrap, int bias, const 
   return "";
 }
 
+// The gather's lists ordered for the interpolation by tiles: within each tile
+// by which halves of the tile's a1 side the footprint reaches, then by its a0
+// start, then in list order, so that consecutive entries reach the same points.
+// pos (nlist) gets each list position's place in the new order; the node-major
+// index is moved along.
+// tneed gets, for every 16 consecutive entries of a tile (tiles start afresh,
+// at tgroup), bit x + 8 h if one of their footprints reaches the tile's points
+// (x, y) with y in [4h, 4h + 4) (all of them when starts are modulo nf).
+inline void order_tiles(const Geometry& g, bool nowrap, int bias, const std::vector<int64_t>& tcount,
+                        const std::vector<Entry>& list, std::vector<Entry>& tlist, std::vector<int>& npos,
+                        std::vector<int64_t>& tgroup, std::vector<int>& tneed, int threads = 1) {
+  const int64_t ntiles = (int64_t)tcount.size() - 1, nlist = tcount[ntiles];
+  tlist.assign(list.size(), Entry{0, 0});
+  std::vector<int> pos(nlist);
+  tgroup.assign(ntiles + 1, 0);
+  for (int64_t t = 0; t < ntiles; ++t) tgroup[t + 1] = tgroup[t] + (tcount[t + 1] - tcount[t] + 15) / 16;
+  tneed.assign(std::max<int64_t>(tgroup[ntiles], 1), nowrap ? 0 : 0xffff);
+  auto reach = [&](const Entry& e) {
+    const int ex = (e.code & 1023) - bias, ey = ((e.code >> 10) & 1023) - bias;
+    int mx = 0, m = 0;
+    for (int x = std::max(ex, 0); x < std::min(ex + g.w[0], g.T[0]); ++x) mx |= 1 << x;
+    for (int h = 0; h < 2; ++h)
+      if (ey < 4 * h + 4 && ey + g.w[1] > 4 * h) m |= mx << (8 * h);
+    return m;
+  };
+  const int half = g.T[1] / 2;
+  // key: 3 classes of the a1 side times the a0 starts
+  const int nx = nowrap ? g.T[0] + g.w[0] - 1 : g.nf[0];
+  auto key = [&](const Entry& e) {
+    int ex = e.code & 1023, ey = (e.code >> 10) & 1023, c = 0;
+    if (nowrap) {
+      ex += g.w[0] - 1 - bias;
+      ey -= bias;
+      c = ey >= half ? 2 : (ey + g.w[1] <= half ? 0 : 1);
+    }
+    return c * nx + ex;
+  };
+  parallel_ranges(ntiles, threads, [&](int64_t b, int64_t e, int) {
+    std::vector<int64_t> at(3 * nx + 1);
+    for (int64_t tile = b; tile < e; ++tile) {
+      std::fill(at.begin(), at.end(), 0);
+      for (int64_t i = tcount[tile]; i < tcount[tile + 1]; ++i) at[key(list[i]) + 1]++;
+      for (int k = 0; k < 3 * nx; ++k) at[k + 1] += at[k];
+      for (int64_t i = tcount[tile]; i < tcount[tile + 1]; ++i) {
+        const int64_t k = tcount[tile] + at[key(list[i])]++;
+        tlist[k] = list[i];
+        pos[i] = (int)k;
+        if (nowrap) tneed[tgroup[tile] + (k - tcount[tile]) / 16] |= reach(list[i]);
+      }
+    }
+  });
+  parallel_ranges(nlist, threads, [&](int64_t b, int64_t e, int) {
+    for (int64_t i = b; i < e; ++i) npos[i] = pos[npos[i]];
+  });
+}
+
 // The ring lists (see above).  perm[j] is node j's natural half index
 // ((a n_theta + b) nph2 + l); nrings = n_r n_theta.  rnodes gets the entries
 // (each ring's last carries 1 << end_bit and its a2 start code << z_bit;

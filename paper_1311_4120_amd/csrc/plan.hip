@@ -251,6 +251,31 @@ void spread_items(const Plan& pl, int chunk, std::vector<WorkItem>& items, std::
                          WorkItem{-1, 0, 0, -1}, key);
 }
 
+// Work items of the interpolation by tiles, one per wavefront: a tile's list
+// in runs of at most kTileItem entries, fewer where the lists are too short to
+// give every wavefront slot of the device an item (each entry's share is stored
+// on its own, so a split costs no more than another read of the tile's grid
+// values and a wavefront's start: its item, then the entries and the grid
+// values, then the first records, three dependent round trips to memory).
+std::vector<TileItem> tile_items(const Plan& pl, const std::vector<int64_t>& tgroup) {
+  constexpr int kSlots = 4096;  // 256 CUs, four SIMDs each, four wavefronts in flight
+  const int64_t nlist = pl.h_tcount[pl.ngtiles];
+  const int cap = (int)std::min<int64_t>(kTileItem, std::max<int64_t>(64, nlist / kSlots / 16 * 16));
+  std::vector<TileItem> items;
+  for (int tile = 0; tile < pl.ngtiles; ++tile) {
+    const int t2 = tile % pl.gnt[2], t1 = tile / pl.gnt[2] % pl.gnt[1], t0 = tile / (pl.gnt[1] * pl.gnt[2]);
+    const int64_t b0 = pl.h_tcount[tile], e0 = pl.h_tcount[tile + 1];
+    for (int64_t b = b0; b < e0; b += cap)
+      items.push_back(TileItem{(uint16_t)t0, (uint16_t)t1, (uint16_t)t2, (uint16_t)std::min<int64_t>(cap, e0 - b), (int)b,
+                               (int)(tgroup[tile] + (b - b0) / 16)});
+  }
+  auto key = [](const TileItem& it) { return morton3(it.t0, it.t1, it.t2); };
+  const TileItem idle{0, 0, 0, 0, 0, 0};
+  items = dispatch_order(items, [](const TileItem& it) { return (double)it.count; }, idle, key);
+  items.resize((items.size() + 8 * kTileWaves - 1) / (8 * kTileWaves) * (8 * kTileWaves), idle);
+  return items;
+}
+
 // Work items of the spreading by rings: one per ring tile, tiles whose rings
 // cost more than chunk split at ring boundaries into items that write
 // partial tiles (cost: node entries plus kRingEntryCost per ring); each item's
@@ -486,6 +511,23 @@ Status time_stage(Plan& pl, bool interp, double& best_ms) {
   return Status::ok();
 }
 
+// What the tuner takes in JGB_MIXED.  There the form and the chunk of a sum
+// decide its last digits (E by some 1e-7), unlike in float64, and a program's
+// results should not move with the speed of a kernel or the noise of a timing.
+// The interpolation and the ring chunk therefore follow the node count and the
+// grid, along the lines where the staged interpolation and the tiles, and one
+// chunk and the next, were once measured equal; the rings must beat the gather
+// by a margin.  (Today's tiles win between the lines too, by 15 to 50%: a
+// program that wants them asks for JGB_FLAG_INTERP_TILES.)
+bool mixed_tiles(const Plan& pl) {
+  const int64_t points = (int64_t)pl.n[0] * pl.n[1] * pl.n[2];
+  return pl.split || pl.Mh <= 8000 || (pl.Mh <= 16000 && points <= 42000) || pl.Mh >= 500000;
+}
+int mixed_ring_chunk(int64_t Mh) {
+  return Mh <= kSmallNodeSet ? 512 : Mh < 224000 ? 2048 : Mh < 600000 ? 4096 : 8192;
+}
+constexpr double kMixedRingMargin = 1.1;
+
 Status autotune(Plan& pl) {
   const char* path = getenv("JGB_AUTOTUNE_CACHE");
   const std::string key = tune_key(pl);
@@ -515,7 +557,10 @@ Status autotune(Plan& pl) {
     }
   }
   TRY(apply_interp_chunk(pl, ic));
-  if (pl.tile_ok && !(pl.p.flags & JGB_FLAG_INTERP_TILES)) {
+  if (pl.tile_ok && !pl.fp64 && !forced) {
+    pl.tile_interp = mixed_tiles(pl);
+    if (pl.tile_interp) ic = kTileInterp;
+  } else if (pl.tile_ok && !forced) {
     // the interpolation by tiles on the matrix cores, against the best chunk
     pl.tile_interp = true;
     double ms;
@@ -549,7 +594,7 @@ Status autotune(Plan& pl) {
     int rc = 0;
     double best_r = 1e30;
     for (int c : kRingChunks) {
-      if (c < min_ring_chunk(pl.Mh)) continue;
+      if (c < min_ring_chunk(pl.Mh) || (!pl.fp64 && c != mixed_ring_chunk(pl.Mh))) continue;
       TRY(apply_ring_chunk(pl, c));
       double ms;
       TRY(pl.fp64 ? time_stage<double>(pl, false, ms) : time_stage<float>(pl, false, ms));
@@ -559,7 +604,7 @@ Status autotune(Plan& pl) {
       }
     }
     TRY(apply_ring_chunk(pl, rc));
-    if (best_r < best_s || forced_rings) {
+    if (best_r * (pl.fp64 ? 1.0 : kMixedRingMargin) < best_s || forced_rings) {
       best_s = best_r;
       sc = -rc;
     } else {
@@ -929,20 +974,29 @@ Status build_plan(Plan& pl, const jgb_params* p) {
   std::vector<int64_t> tcount;
   std::vector<lists::Entry> list;
   std::vector<int> nstart, npos;
+  std::vector<int64_t> tgroup;
+  lists::Geometry g{};
+  for (int a = 0; a < 3; ++a) {
+    g.nf[a] = pl.nf[a];
+    g.T[a] = pl.GT[a];
+    g.nt[a] = pl.gnt[a];
+    g.w[a] = pl.w[a];
+  }
   {
-    lists::Geometry g{};
-    for (int a = 0; a < 3; ++a) {
-      g.nf[a] = pl.nf[a];
-      g.T[a] = pl.GT[a];
-      g.nt[a] = pl.gnt[a];
-      g.w[a] = pl.w[a];
-    }
     const std::string err =
         lists::gather_lists(g, pl.gather_nowrap, kGatherBias, hdr, tcount, list, pl.tile_ok, nstart, npos, host_threads());
     if (!err.empty()) return fail(JGB_ERR_UNSUPPORTED, err);
   }
   const int64_t nlist = tcount[pl.ngtiles];
   if (pl.tile_ok) {
+    // the interpolation's own order of each tile's list
+    std::vector<lists::Entry> tlist;
+    std::vector<int> tneed;
+    lists::order_tiles(g, pl.gather_nowrap, kGatherBias, tcount, list, tlist, npos, tgroup, tneed, host_threads());
+    TRY(dev_alloc(pl, &pl.d_tneed, sizeof(int) * tneed.size()));
+    TRY(upload(pl, pl.d_tneed, tneed.data(), sizeof(int) * tneed.size()));
+    TRY(dev_alloc(pl, &pl.d_tlist, sizeof(lists::Entry) * tlist.size()));
+    TRY(upload(pl, pl.d_tlist, tlist.data(), sizeof(lists::Entry) * tlist.size()));
     TRY(dev_alloc(pl, &pl.d_nstart, sizeof(int) * (Mh + 1)));
     TRY(upload(pl, pl.d_nstart, nstart.data(), sizeof(int) * (Mh + 1)));
     TRY(dev_alloc(pl, &pl.d_npos, sizeof(int) * std::max<int64_t>(nlist, 1)));
@@ -955,6 +1009,12 @@ Status build_plan(Plan& pl, const jgb_params* p) {
   pl.nlist = nlist;
 
   pl.h_tcount = tcount;
+  if (pl.tile_ok) {
+    const std::vector<TileItem> ti = tile_items(pl, tgroup);
+    TRY(dev_alloc(pl, &pl.d_titems, sizeof(TileItem) * std::max<size_t>(ti.size(), 1)));
+    if (!ti.empty()) TRY(upload(pl, pl.d_titems, ti.data(), sizeof(TileItem) * ti.size()));
+    pl.ntitems = (int)ti.size();
+  }
   if (pl.r2c) {
     // the spreading grid's reach per line of the inverse's first pass (axis
     // 0 in 3D, axis 1 in 2D): that pass reads zero beyond it
@@ -976,13 +1036,6 @@ Status build_plan(Plan& pl, const jgb_params* p) {
     // the spectrum's reach per line of the forward transform's last pass,
     // from the tiles the interpolation by tiles reads: that pass stores
     // nothing beyond it when the interpolation runs by tiles
-    lists::Geometry g{};
-    for (int a = 0; a < 3; ++a) {
-      g.nf[a] = pl.nf[a];
-      g.T[a] = pl.GT[a];
-      g.nt[a] = pl.gnt[a];
-      g.w[a] = pl.w[a];
-    }
     std::vector<lists::Extent> ext;
     const std::string err = lists::tile_read_extents(g, tcount, pl.r2c, ext, host_threads());
     if (!err.empty()) return fail(JGB_ERR_UNSUPPORTED, err);
