@@ -511,22 +511,31 @@ Status time_stage(Plan& pl, bool interp, double& best_ms) {
   return Status::ok();
 }
 
-// What the tuner takes in JGB_MIXED.  There the form and the chunk of a sum
+// What a tuned plan takes in JGB_MIXED.  There the form and the chunk of a sum
 // decide its last digits (E by some 1e-7), unlike in float64, and a program's
 // results should not move with the speed of a kernel or the noise of a timing.
-// The interpolation and the ring chunk therefore follow the node count and the
-// grid, along the lines where the staged interpolation and the tiles, and one
-// chunk and the next, were once measured equal; the rings must beat the gather
-// by a margin.  (Today's tiles win between the lines too, by 15 to 50%: a
+// They therefore follow the node count, the length of the tiles' lists and the
+// grid, along the lines where the staged interpolation and the tiles, the
+// gather and the rings, and one chunk and the next, were once measured equal
+// on 122 node sets.  (Today's tiles win between the lines too, by 15 to 50%: a
 // program that wants them asks for JGB_FLAG_INTERP_TILES.)
 bool mixed_tiles(const Plan& pl) {
   const int64_t points = (int64_t)pl.n[0] * pl.n[1] * pl.n[2];
-  return pl.split || pl.Mh <= 8000 || (pl.Mh <= 16000 && points <= 42000) || pl.Mh >= 500000;
+  return pl.split || pl.Mh <= 8000 || (pl.Mh <= 16000 && points <= 42000) || pl.Mh >= 500000 || pl.nlist >= 3360000;
 }
-int mixed_ring_chunk(int64_t Mh) {
-  return Mh <= kSmallNodeSet ? 512 : Mh < 224000 ? 2048 : Mh < 600000 ? 4096 : 8192;
+bool mixed_rings(const Plan& pl) {
+  // a side that ends inside a ring tile costs the rings more than the gather,
+  // until the lists are long
+  const bool ragged = pl.nf[0] % kRingTile0 != 0;
+  return pl.Mh > kSmallNodeSet && !(ragged && pl.nlist >= 500000 && pl.nlist < 1400000);
 }
-constexpr double kMixedRingMargin = 1.1;
+int mixed_ring_chunk(const Plan& pl) {
+  return pl.Mh <= kSmallNodeSet ? 512 : pl.nlist < 1330000 ? 2048 : pl.nlist < 3360000 ? 4096 : pl.nlist < 10000000 ? 8192 : 16384;
+}
+int mixed_spread_chunk(const Plan& pl) {
+  const int c = pl.nlist < 170000 ? 256 : pl.Mh <= kSmallNodeSet ? 512 : 1024;
+  return std::max(c, min_spread_chunk(pl.Mh));
+}
 
 Status autotune(Plan& pl) {
   const char* path = getenv("JGB_AUTOTUNE_CACHE");
@@ -564,7 +573,7 @@ Status autotune(Plan& pl) {
     // the interpolation by tiles on the matrix cores, against the best chunk
     pl.tile_interp = true;
     double ms;
-    TRY(pl.fp64 ? time_stage<double>(pl, true, ms) : time_stage<float>(pl, true, ms));
+    TRY(time_stage<double>(pl, true, ms));
     if (ms < best_i) {
       best_i = ms;
       ic = kTileInterp;
@@ -572,15 +581,24 @@ Status autotune(Plan& pl) {
       pl.tile_interp = false;
     }
   }
+  if (!pl.fp64) {
+    pl.ring_spread = pl.ring_ok && (forced_rings || mixed_rings(pl));
+    sc = pl.ring_spread ? -mixed_ring_chunk(pl) : mixed_spread_chunk(pl);
+    TRY(sc < 0 ? apply_ring_chunk(pl, -sc) : apply_spread_chunk(pl, sc));
+    TRY(time_stage<float>(pl, true, best_i));  // node values for spreading
+    TRY(time_stage<float>(pl, false, best_s));
+    if (path) cache_store(path, key, ic, sc, best_i, best_s);
+    return Status::ok();
+  }
   double ms0;
-  TRY(pl.fp64 ? time_stage<double>(pl, true, ms0) : time_stage<float>(pl, true, ms0));  // node values for spreading
+  TRY(time_stage<double>(pl, true, ms0));  // node values for spreading
   pl.ring_spread = false;
   if (!forced_rings) {
     for (int c : kSpreadChunks) {
       if (c < min_spread_chunk(pl.Mh)) continue;
       TRY(apply_spread_chunk(pl, c));
       double ms;
-      TRY(pl.fp64 ? time_stage<double>(pl, false, ms) : time_stage<float>(pl, false, ms));
+      TRY(time_stage<double>(pl, false, ms));
       if (ms < best_s) {
         best_s = ms;
         sc = c;
@@ -594,17 +612,17 @@ Status autotune(Plan& pl) {
     int rc = 0;
     double best_r = 1e30;
     for (int c : kRingChunks) {
-      if (c < min_ring_chunk(pl.Mh) || (!pl.fp64 && c != mixed_ring_chunk(pl.Mh))) continue;
+      if (c < min_ring_chunk(pl.Mh)) continue;
       TRY(apply_ring_chunk(pl, c));
       double ms;
-      TRY(pl.fp64 ? time_stage<double>(pl, false, ms) : time_stage<float>(pl, false, ms));
+      TRY(time_stage<double>(pl, false, ms));
       if (ms < best_r) {
         best_r = ms;
         rc = c;
       }
     }
     TRY(apply_ring_chunk(pl, rc));
-    if (best_r * (pl.fp64 ? 1.0 : kMixedRingMargin) < best_s || forced_rings) {
+    if (best_r < best_s || forced_rings) {
       best_s = best_r;
       sc = -rc;
     } else {

@@ -124,11 +124,12 @@ __device__ __forceinline__ float row_shr8(float v) {
 template <typename T>
 struct GatherLds {
   static __host__ __device__ int wave_values(int lstride) {  // T values per wave, 16-byte multiple
-    return 16 * lstride + 32 + 32 * (int)(sizeof(int2) / sizeof(T));
+    return 16 * lstride + 32 + 64 / (int)sizeof(T);
   }
 };
 
-template <typename T, int T1, bool NOWRAP>
+// NF: 16-byte pieces of a record each lane fetches, ceil(record pieces / 4).
+template <typename T, int T1, bool NOWRAP, int NF>
 __device__ __forceinline__ void gather_body(const SpreadArgs<T>& a, const int blk) {
   typedef typename Mfma<T>::acc_t acc_t;
   constexpr int T0 = 64 / T1;
@@ -148,10 +149,10 @@ __device__ __forceinline__ void gather_body(const SpreadArgs<T>& a, const int bl
   const int zl = li & (kGatherZ - 1);            // tile z of the lane's column
   const int upart = li >= kGatherZ ? 1 : 0;      // imaginary part
   const int W = a.width;
-  // the wave's staging area: 16 records, 16 weighted values, 16 entries
+  // the wave's staging area: 16 records, 16 weighted values, 16 entry codes
   T* recs = reinterpret_cast<T*>(smem_raw) + (size_t)wave * GatherLds<T>::wave_values(a.lstride);
   T* uh = recs + 16 * a.lstride;
-  int2* ents = reinterpret_cast<int2*>(uh + 32);
+  int* codes = reinterpret_cast<int*>(uh + 32);
 
   // the lane's x values (per row block when NX = 4) and y values (per row
   // block when NY = 4); points off the grid never take a value
@@ -182,35 +183,60 @@ __device__ __forceinline__ void gather_body(const SpreadArgs<T>& a, const int bl
   const int kb = wave < nw ? item.vbegin + wave * q : item.vend;
   const int ke = (kb + q < item.vend) ? kb + q : item.vend;
 
+  // entries g .. g + 15 reach LDS through registers, one batch ahead: lane
+  // 16k + i fetches the pieces k, k + 4, ... of record i (a lane without a
+  // piece the last one again), its weighted value and, another batch ahead, its
+  // entry.  Lanes past the end fetch entry ke - 1, whose kernel values the
+  // groups below then never use.  Unconditional loads: see the rings.  Untuned
+  // 90 x 60 x 108, 155 520 nodes, float64: 197 us with the batch loaded where
+  // it is used, 95 one batch ahead (its bound: sixteen products of 64 cycles a batch,
+  // most of them on points off the footprints).
   constexpr int kChunk = 16 / sizeof(T);
   const int nchunk = a.rstride / kChunk;
   const uint32_t rbytes = (uint32_t)(a.rstride * sizeof(T));
+  typedef uint32_t piece_t __attribute__((ext_vector_type(4)));
+  piece_t pre[NF];
+  int off[NF];
+#pragma unroll
+  for (int m = 0; m < NF; ++m) off[m] = min(lk + 4 * m, nchunk - 1) * 16;
+  T* const myrec = recs + li * a.lstride;
+  C2<T> pu{T(0), T(0)};
+  int2 ent0{0, 0}, ent1{0, 0};
+#define JGB_GATHER_ENTRY(g) load_at<int2>(a.list, (uint32_t)min((g) + li, ke - 1) * 8u)
+#define JGB_GATHER_FETCH(node)                                                                   \
+  do {                                                                                           \
+    const uint32_t rec_ = (uint32_t)(node) * rbytes;                                             \
+    _Pragma("unroll") for (int m = 0; m < NF; ++m)                                               \
+      pre[m] = load_at<piece_t>(a.wts, rec_ + (uint32_t)off[m]);                                 \
+    pu = load_at<C2<T>>(a.uhat, (uint32_t)(node) * (uint32_t)sizeof(C2<T>));                     \
+  } while (0)
+  if (kb < ke) {
+    ent0 = JGB_GATHER_ENTRY(kb);
+    ent1 = JGB_GATHER_ENTRY(kb + 16);
+    JGB_GATHER_FETCH(ent0.x);
+  }
   for (int g = kb; g < ke; g += 16) {
-    // stage entries g .. g + 15 (lanes past the end copy entry ke - 1, whose
-    // kernel values the groups below then never use)
-    {
-      const int e16 = g + li;
-      const int2 ent = load_at<int2>(a.list, (uint32_t)(e16 < ke ? e16 : ke - 1) * 8u);
-      const uint32_t rec = (uint32_t)ent.x * rbytes;
-      __builtin_amdgcn_wave_barrier();  // the previous batch's reads are done
-      for (int c = lk; c < nchunk; c += 4)
-        *reinterpret_cast<uint4*>(recs + li * a.lstride + c * kChunk) = load_at<uint4>(a.wts, rec + (uint32_t)c * 16u);
-      if (lk == 0) {
-        // an entry past the end contributes nothing: its weighted value is zero
-        const C2<T> u = load_at<C2<T>>(a.uhat, (uint32_t)ent.x * (uint32_t)sizeof(C2<T>));
-        *reinterpret_cast<C2<T>*>(uh + 2 * li) = e16 < ke ? u : C2<T>{T(0), T(0)};
-        ents[li] = ent;
-      }
-      __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_wave_barrier();  // the previous batch's reads are done
+#pragma unroll
+    for (int m = 0; m < NF; ++m)
+      *reinterpret_cast<piece_t*>(reinterpret_cast<unsigned char*>(myrec) + off[m]) = pre[m];
+    if (lk == 0) {
+      // an entry past the end contributes nothing: its weighted value is zero
+      *reinterpret_cast<C2<T>*>(uh + 2 * li) = g + li < ke ? pu : C2<T>{T(0), T(0)};
+      codes[li] = ent0.y;
     }
+    __builtin_amdgcn_wave_barrier();
+    JGB_GATHER_FETCH(ent1.x);
+    ent0.y = ent1.y;
+    ent1 = JGB_GATHER_ENTRY(g + 32);
     // the groups of four that hold entries (the count is uniform over the wave)
     const int ngq = min(4, (ke - g + 3) >> 2);
 #pragma unroll
     for (int gq = 0; gq < 4; ++gq) {
       if (gq >= ngq) break;
       const int e = 4 * gq + lk;
-      const int2 ent = ents[e];
-      const int ex = ent.y & 1023, ey = (ent.y >> 10) & 1023, ez = (ent.y >> 20) & 1023;
+      const int code = codes[e];
+      const int ex = code & 1023, ey = (code >> 10) & 1023, ez = (code >> 20) & 1023;
       const T* rr = recs + e * a.lstride;
       // tap d = (p - start) mod nf of a point p covers it iff d < w (w <= nf);
       // with signed starts d = p - start, and a negative d is a large unsigned
@@ -232,6 +258,8 @@ __device__ __forceinline__ void gather_body(const SpreadArgs<T>& a, const int bl
     }
   }
 
+#undef JGB_GATHER_FETCH
+#undef JGB_GATHER_ENTRY
   // fixed-order sum of the active wavefronts' partial tiles: w0 alone,
   // w0 + w1, or (w0 + w2) + (w1 + w3); the staging area is reused
   __syncthreads();
@@ -291,16 +319,16 @@ __device__ __forceinline__ void gather_body(const SpreadArgs<T>& a, const int bl
     }
 }
 
-template <typename T, int T1, bool NOWRAP>
+template <typename T, int T1, bool NOWRAP, int NF>
 __global__ void __launch_bounds__(256) k_spread_gather(SpreadArgs<T> a) {
-  gather_body<T, T1, NOWRAP>(a, blockIdx.x);
+  gather_body<T, T1, NOWRAP, NF>(a, blockIdx.x);
 }
-template <typename T, int T1, bool NOWRAP>
+template <typename T, int T1, bool NOWRAP, int NF>
 __global__ void __launch_bounds__(256) k_spread_gather_b(const SpreadArgs<T>* __restrict__ tab, const int* __restrict__ bstart, int nm) {
   int m;
   const int blk = batch_block(bstart, nm, blockIdx.x, m);
   if (blk < 0) return;
-  gather_body<T, T1, NOWRAP>(tab[m], blk);
+  gather_body<T, T1, NOWRAP, NF>(tab[m], blk);
 }
 
 // Sum the partial tiles of each split tile in slot order and store the tile.
@@ -414,6 +442,27 @@ int gather_lds_stride(int rstride) {
   return rstride;
 }
 
+template <typename T, int T1, bool NOWRAP>
+hipError_t launch_gather(const SpreadArgs<T>& a, unsigned blocks, size_t smem, hipStream_t s) {
+  typedef SpreadArgs<T> A;
+  // a record has 3 (w + 1) values, 4 to 13 pieces in float32 and up to 26 in float64
+#define JGB_GATHER_CASE(NF) \
+  case NF:                  \
+    return launch<A, k_spread_gather<T, T1, NOWRAP, NF>, k_spread_gather_b<T, T1, NOWRAP, NF>>(a, blocks, 256, smem, s);
+  switch ((a.rstride * (int)sizeof(T) / 16 + 3) / 4) {
+    JGB_GATHER_CASE(1) JGB_GATHER_CASE(2) JGB_GATHER_CASE(3) JGB_GATHER_CASE(4)
+    case 5:
+    case 6:
+    case 7:
+      if constexpr (sizeof(T) == 8) {
+        switch ((a.rstride * (int)sizeof(T) / 16 + 3) / 4) { JGB_GATHER_CASE(5) JGB_GATHER_CASE(6) JGB_GATHER_CASE(7) }
+      }
+      [[fallthrough]];
+    default: return hipErrorInvalidValue;
+  }
+#undef JGB_GATHER_CASE
+}
+
 template <typename T>
 hipError_t launch_spread(const Plan& pl, hipStream_t s) {
   if (pl.ring_spread) return launch_ring_spread<T>(pl, s);
@@ -441,20 +490,12 @@ hipError_t launch_spread(const Plan& pl, hipStream_t s) {
   stage_mark(pl, ST_SPREAD, 0, s);
   const size_t smem = std::max((size_t)kWaves * GatherLds<T>::wave_values(a.lstride), (size_t)2 * 4 * 4 * 64) * sizeof(T);
   hipError_t e;
-  typedef SpreadArgs<T> A;
-  if (pl.GT[0] == 8 && pl.GT[1] == 8) {
-    if (pl.gather_nowrap)
-      e = launch<A, k_spread_gather<T, 8, true>, k_spread_gather_b<T, 8, true>>(a, blocks, 256, smem, s);
-    else
-      e = launch<A, k_spread_gather<T, 8, false>, k_spread_gather_b<T, 8, false>>(a, blocks, 256, smem, s);
-  } else if (pl.GT[0] == 1 && pl.GT[1] == 64) {
-    if (pl.gather_nowrap)
-      e = launch<A, k_spread_gather<T, 64, true>, k_spread_gather_b<T, 64, true>>(a, blocks, 256, smem, s);
-    else
-      e = launch<A, k_spread_gather<T, 64, false>, k_spread_gather_b<T, 64, false>>(a, blocks, 256, smem, s);
-  } else {
+  if (pl.GT[0] == 8 && pl.GT[1] == 8)
+    e = pl.gather_nowrap ? launch_gather<T, 8, true>(a, blocks, smem, s) : launch_gather<T, 8, false>(a, blocks, smem, s);
+  else if (pl.GT[0] == 1 && pl.GT[1] == 64)
+    e = pl.gather_nowrap ? launch_gather<T, 64, true>(a, blocks, smem, s) : launch_gather<T, 64, false>(a, blocks, smem, s);
+  else
     return hipErrorInvalidValue;
-  }
   stage_mark(pl, ST_SPREAD, 1, s);
   if (e != hipSuccess || pl.nmulti == 0) return e;
   stage_mark(pl, ST_SPREAD_REDUCE, 0, s);
