@@ -135,7 +135,7 @@ __device__ __forceinline__ void ring_gather_body(const RingArgs<T>& a, const int
   const int W = a.width;
   T* recs = reinterpret_cast<T*>(smem_raw) + (size_t)wave * RingLds<T>::values(a.lstride);
   T* uh = recs + 16 * a.lstride;
-  int* codes = reinterpret_cast<int*>(uh + 32);  // entry 4q + k at [4 k + q]
+  int* codes = reinterpret_cast<int*>(uh + 32);  // a batch ahead of the records: entry 4q + k at [4 k + q]
 
   // operands of the node products: lane 16k + i takes a0 tap x = i of node k
   // (A) and the a1 tap y = i / 2 of node k times part i mod 2 of its weighted
@@ -152,6 +152,10 @@ __device__ __forceinline__ void ring_gather_body(const RingArgs<T>& a, const int
 
   constexpr int kChunk = 16 / sizeof(T);
   constexpr int kFetch = NF;
+  // points of axis 2 per test whether a ring reaches them (off its footprint
+  // the a2 values are zero): 128^3, float64 and float32, 255 and 88 us with one
+  // point a test, 247 and 85 with two, no better with four
+  constexpr int kZTest = 2;
   const int nchunk_xy = (2 * (W + 1) + kChunk - 1) / kChunk;  // a record's a0 and a1 values
   const int nchunk_all = (3 * (W + 1) + kChunk - 1) / kChunk;  // and its a2 values
   const uint32_t rbytes = (uint32_t)(a.rstride * sizeof(T));
@@ -165,7 +169,12 @@ __device__ __forceinline__ void ring_gather_body(const RingArgs<T>& a, const int
   // load is conditional: where one was, the compiler waited for it at the end
   // of the condition, at once, instead of a batch later.  128^3, 1 048 576
   // nodes: float64 293 us -> 245, float32 100 -> 87; 256^3, 8 388 608 nodes,
-  // float32 753 -> 607.
+  // float32 753 -> 607.  The entry codes reach LDS a batch ahead as well, so
+  // that the taps' addresses do not wait for them.  What bounds it now is the
+  // issue of instructions, not memory (with every record in cache float64
+  // gains 5%, float32 nothing): in float32 some instruction issues in nearly
+  // every cycle, half of them vector arithmetic; float64 has two wavefronts a
+  // SIMD, for its 128 registers of tile sums.
   const int ebeg = item.e[wave], eend = item.e[wave + 1];
   const int ngroups = (eend - ebeg) >> 2;
   acc_t H = acc_t{T(0), T(0), T(0), T(0)};
@@ -186,7 +195,11 @@ __device__ __forceinline__ void ring_gather_body(const RingArgs<T>& a, const int
     ent = JGB_RING_ENTRY(0);
     ent_next = JGB_RING_ENTRY(4);
     JGB_RING_FETCH(ent);
+    codes[4 * (li & 3) + (li >> 2)] = ent.y;
   }
+  __builtin_amdgcn_wave_barrier();
+  // the batch's codes of entries lk, 4 + lk, 8 + lk, 12 + lk
+  int4 cq = *reinterpret_cast<const int4*>(codes + 4 * lk);
 
   for (int gb = 0; gb < ngroups; gb += 4) {
     __builtin_amdgcn_wave_barrier();  // the previous batch's reads are done
@@ -197,16 +210,15 @@ __device__ __forceinline__ void ring_gather_body(const RingArgs<T>& a, const int
       if (lk == 0) {
         uh[2 * li] = pu.x;
         uh[2 * li + 1] = pu.y;
-        codes[4 * (li & 3) + (li >> 2)] = ent.y;
       }
     }
     __builtin_amdgcn_wave_barrier();
+    const int cv[4] = {cq.x, cq.y, cq.z, cq.w};
+    codes[4 * (li & 3) + (li >> 2)] = ent_next.y;
     JGB_RING_FETCH(ent_next);
     ent.y = ent_next.y;
     ent_next = JGB_RING_ENTRY(gb + 8);
     // the four groups' operands
-    const int4 cq = *reinterpret_cast<const int4*>(codes + 4 * lk);
-    const int cv[4] = {cq.x, cq.y, cq.z, cq.w};
     T av[4], bv[4], pz[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
@@ -220,6 +232,8 @@ __device__ __forceinline__ void ring_gather_body(const RingArgs<T>& a, const int
       const int zc = (__builtin_amdgcn_readlane(cv[q], 48) >> kRingZBit) & 1023;
       pz[q] = recs[(4 * q + 3) * a.lstride + 2 * (W + 1) + min((uint32_t)(li + kGatherBias - zc), (uint32_t)W)];
     }
+    __builtin_amdgcn_wave_barrier();
+    cq = *reinterpret_cast<const int4*>(codes + 4 * lk);  // the next batch's
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       if (gb + q >= ngroups) break;
@@ -230,11 +244,14 @@ __device__ __forceinline__ void ring_gather_body(const RingArgs<T>& a, const int
       if ((cl >> kRingEndBit) & 1) {
         const int zoff = kGatherBias - ((cl >> kRingZBit) & 1023);  // tap of tile point z: z + zoff
 #pragma unroll
-        for (int z = 0; z < RZ; ++z) {
-          if ((unsigned)(z + zoff) < (unsigned)W) {
-            const T p = lane_value(pz[q], z);
+        for (int z = 0; z < RZ; z += kZTest) {
+          if ((unsigned)(z + kZTest - 1 + zoff) < (unsigned)(W + kZTest - 1)) {
 #pragma unroll
-            for (int r = 0; r < 4; ++r) g[r][z] += H[r] * p;
+            for (int zz = z; zz < z + kZTest; ++zz) {
+              const T p = lane_value(pz[q], zz);
+#pragma unroll
+              for (int r = 0; r < 4; ++r) g[r][zz] += H[r] * p;
+            }
           }
         }
         H = acc_t{T(0), T(0), T(0), T(0)};
