@@ -33,6 +33,7 @@
 #include <algorithm>
 #include <atomic>
 #include <cstdint>
+#include <memory>
 #include <string>
 #include <thread>
 #include <vector>
@@ -186,17 +187,16 @@ inline std::string gather_lists(const Geometry& g, bool nowrap, int bias, const 
 // The gather's lists ordered for the interpolation by tiles: within each tile
 // by which halves of the tile's a1 side the footprint reaches, then by its a0
 // start, then in list order, so that consecutive entries reach the same points.
-// pos (nlist) gets each list position's place in the new order; the node-major
-// index is moved along.
+// tlist gets as many entries as tcount ends at; the node-major index is moved
+// along.
 // tneed gets, for every 16 consecutive entries of a tile (tiles start afresh,
 // at tgroup), bit x + 8 h if one of their footprints reaches the tile's points
 // (x, y) with y in [4h, 4h + 4) (all of them when starts are modulo nf).
 inline void order_tiles(const Geometry& g, bool nowrap, int bias, const std::vector<int64_t>& tcount,
-                        const std::vector<Entry>& list, std::vector<Entry>& tlist, std::vector<int>& npos,
+                        const std::vector<Entry>& list, Entry* tlist, std::vector<int>& npos,
                         std::vector<int64_t>& tgroup, std::vector<int>& tneed, int threads = 1) {
   const int64_t ntiles = (int64_t)tcount.size() - 1, nlist = tcount[ntiles];
-  tlist.assign(list.size(), Entry{0, 0});
-  std::vector<int> pos(nlist);
+  const std::unique_ptr<int[]> pos(new int[nlist]);  // a list position's place in the new order
   tgroup.assign(ntiles + 1, 0);
   for (int64_t t = 0; t < ntiles; ++t) tgroup[t + 1] = tgroup[t] + (tcount[t + 1] - tcount[t] + 15) / 16;
   tneed.assign(std::max<int64_t>(tgroup[ntiles], 1), nowrap ? 0 : 0xffff);

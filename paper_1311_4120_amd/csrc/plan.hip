@@ -1008,13 +1008,13 @@ Status build_plan(Plan& pl, const jgb_params* p) {
   const int64_t nlist = tcount[pl.ngtiles];
   if (pl.tile_ok) {
     // the interpolation's own order of each tile's list
-    std::vector<lists::Entry> tlist;
+    const std::unique_ptr<lists::Entry[]> tlist(new lists::Entry[std::max<int64_t>(nlist, 1)]);
     std::vector<int> tneed;
-    lists::order_tiles(g, pl.gather_nowrap, kGatherBias, tcount, list, tlist, npos, tgroup, tneed, host_threads());
+    lists::order_tiles(g, pl.gather_nowrap, kGatherBias, tcount, list, tlist.get(), npos, tgroup, tneed, host_threads());
     TRY(dev_alloc(pl, &pl.d_tneed, sizeof(int) * tneed.size()));
     TRY(upload(pl, pl.d_tneed, tneed.data(), sizeof(int) * tneed.size()));
-    TRY(dev_alloc(pl, &pl.d_tlist, sizeof(lists::Entry) * tlist.size()));
-    TRY(upload(pl, pl.d_tlist, tlist.data(), sizeof(lists::Entry) * tlist.size()));
+    TRY(dev_alloc(pl, &pl.d_tlist, sizeof(lists::Entry) * std::max<int64_t>(nlist, 1)));
+    if (nlist) TRY(upload(pl, pl.d_tlist, tlist.get(), sizeof(lists::Entry) * nlist));
     TRY(dev_alloc(pl, &pl.d_nstart, sizeof(int) * (Mh + 1)));
     TRY(upload(pl, pl.d_nstart, nstart.data(), sizeof(int) * (Mh + 1)));
     TRY(dev_alloc(pl, &pl.d_npos, sizeof(int) * std::max<int64_t>(nlist, 1)));

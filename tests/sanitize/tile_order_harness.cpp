@@ -32,15 +32,15 @@ int main() {
       for (Start& s : hdr)
         s = Start{(int)(rng() % nf[0]), (int)(rng() % nf[1]), (int)(rng() % nf[2]), 0};
       std::vector<int64_t> tcount, tgroup;
-      std::vector<Entry> list, tlist;
+      std::vector<Entry> list;
       std::vector<int> nstart, npos, tneed;
       if (!gather_lists(g, nowrap, nowrap ? bias : 0, hdr, tcount, list, true, nstart, npos, 3).empty()) return 1;
       const std::vector<int> before = npos;
-      order_tiles(g, nowrap, nowrap ? bias : 0, tcount, list, tlist, npos, tgroup, tneed, 3);
-      std::vector<Entry> serial;
+      std::vector<Entry> tlist(tcount.back()), serial(tcount.back());
+      order_tiles(g, nowrap, nowrap ? bias : 0, tcount, list, tlist.data(), npos, tgroup, tneed, 3);
       std::vector<int> npos1 = before, need1;
       std::vector<int64_t> group1;
-      order_tiles(g, nowrap, nowrap ? bias : 0, tcount, list, serial, npos1, group1, need1, 1);
+      order_tiles(g, nowrap, nowrap ? bias : 0, tcount, list, serial.data(), npos1, group1, need1, 1);
       if (npos1 != npos || need1 != tneed || group1 != tgroup) return 2;
       // every entry once, where the node-major index says
       std::vector<char> hit(tcount.back(), 0);
