@@ -117,9 +117,10 @@ typedef enum { JGB_THETA_GL = 0, JGB_COSTHETA_GL = 1 } jgb_theta_rule;
  * 16x16x4 products of the tile's grid values with the nodes' kernel values --
  * and each node's shares of its tiles are summed in a fixed order.  Without
  * this flag the interpolation stages each sub-bin's neighbourhood in LDS; with
- * JGB_FLAG_AUTOTUNE alone the plan times both and keeps the faster.  Results
- * agree to rounding.  Costs one complex value and one index per list entry of
- * device memory. */
+ * JGB_FLAG_AUTOTUNE alone the plan times both and keeps the faster in
+ * JGB_FP64, and takes one by the node set's size in JGB_MIXED (so that a
+ * result's last digits depend on no timing).  Results agree to rounding.
+ * Costs one complex value and three words per list entry of device memory. */
 #define JGB_FLAG_INTERP_TILES 4u
 /* Spread by rings (3D only, else UNSUPPORTED; also UNSUPPORTED when an
  * oversampled side is shorter than its tile plus the width less one: 16 + w - 1
@@ -128,8 +129,8 @@ typedef enum { JGB_THETA_GL = 0, JGB_COSTHETA_GL = 1 } jgb_theta_rule;
  * not depend on its azimuth: the type-1 front end first sums each ring's
  * nodes over the two other axes on the matrix cores, then spreads each such
  * ring sum along a2 once.  Without this flag the spreading sums every node
- * over all three axes; with JGB_FLAG_AUTOTUNE alone the plan times both and
- * keeps the faster.  Results agree to rounding.  Costs two index tables of
+ * over all three axes; with JGB_FLAG_AUTOTUNE alone the plan takes one as
+ * above.  Results agree to rounding.  Costs two index tables of
  * about one entry per node and touched tile of device memory. */
 #define JGB_FLAG_SPREAD_RINGS 8u
 /* Radial nodes by a generalized Gaussian rule for band-limited integrands

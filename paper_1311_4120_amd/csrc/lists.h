@@ -12,6 +12,9 @@
 //     their a2 footprint), the ring's nodes that touch the tile, each ring
 //     padded to whole groups of four, its last entry flagged and carrying the
 //     ring's a2 start.
+//   order_tiles: the gather lists once more in the order in which the
+//     interpolation by tiles takes them, and which of its matrix products each
+//     group of 16 entries needs.
 //   line_extents: for every line of the spreading grid along the inverse
 //     transform's first axis, the range of positions the nodes' footprints
 //     can reach (the grid is zero elsewhere).
