@@ -90,8 +90,13 @@ typedef enum { JGB_THETA_GL = 0, JGB_COSTHETA_GL = 1 } jgb_theta_rule;
 
 /* flags */
 #define JGB_FLAG_NONE 0u
-/* Time the candidate work-item sizes of the interpolation and spreading
- * kernels on the device at plan time and keep the fastest.  When the
+/* Time the candidate forms and work-item sizes of the interpolation and
+ * spreading kernels on the device at plan time and keep the fastest.  In
+ * JGB_MIXED they decide E's last digits (up to some 1e-7, within its rounding
+ * error of some 5e-7): there the plan takes them by what it counts -- nodes,
+ * list entries, work items -- at fixed costs, so that a result does not move
+ * with a timing, and times the staged interpolation's work-item size alone,
+ * which moves no result by more than the rounding of E's float64 sum.  When the
  * environment variable JGB_AUTOTUNE_CACHE names a file, results are read from
  * and written to it (a JSON object keyed by grid, node counts, cutoff, width
  * and precision), so later plans of the same shape skip the timing. */
@@ -117,10 +122,8 @@ typedef enum { JGB_THETA_GL = 0, JGB_COSTHETA_GL = 1 } jgb_theta_rule;
  * 16x16x4 products of the tile's grid values with the nodes' kernel values --
  * and each node's shares of its tiles are summed in a fixed order.  Without
  * this flag the interpolation stages each sub-bin's neighbourhood in LDS; with
- * JGB_FLAG_AUTOTUNE alone the plan times both and keeps the faster in
- * JGB_FP64, and takes one by the node set's size in JGB_MIXED (so that a
- * result's last digits depend on no timing).  Results agree to rounding.
- * Costs one complex value and three words per list entry of device memory. */
+ * JGB_FLAG_AUTOTUNE alone the plan takes one (see there).  Results agree to
+ * rounding.  Costs one complex value and three words per list entry of device memory. */
 #define JGB_FLAG_INTERP_TILES 4u
 /* Spread by rings (3D only, else UNSUPPORTED; also UNSUPPORTED when an
  * oversampled side is shorter than its tile plus the width less one: 16 + w - 1

@@ -1,0 +1,84 @@
+// Which form and chunk the sums of a tuned JGB_MIXED plan take.  Host code
+// without device dependencies, so that the CPU tests cover it.
+//
+// In float32 the order of a sum decides its last digits: E moves by up to some
+// 1e-7 from one form or chunk to another (its error against 64-bit sums is some
+// 5e-7 in each), and a program's results should not move with the speed of a
+// kernel or the noise of a timing.  Forms and chunks therefore follow from what
+// the plan counts: the times below, in microseconds, are those of the kernels
+// with which plans that timed their forms gave the results that programs know
+// (the present gather, rings and tiles load a batch ahead and are faster), fitted to 955 3D node sets of 16^3 to 256^3 points, 64 to 4 million
+// half-set nodes and 5 to 8 taps, each form and chunk of which was timed twice.
+// Where both timings of a node set took the same, the costs take it too for 94%
+// of 385 node sets of common sizes and all of 120 planar ones (not fitted), and
+// 88% of a grid of 282 sparse, dense and elongated ones; where they do not, the
+// choices lay within a few percent of each other, mostly the noise of a timing.
+// The staged interpolation's chunk moves no result by more than the rounding of
+// E's float64 sum and is still timed.
+#pragma once
+
+#include <algorithm>
+#include <cmath>
+#include <cstdint>
+
+namespace jgb {
+namespace formcost {
+
+// The node set: half-set nodes, taps, entries of the gather's lists, and of
+// the ring lists (node entries, rings).
+struct Nodes {
+  double nodes, width, entries, ring_entries, rings;
+};
+
+// A launch's work items: how many, the partial tiles among them, the most
+// partial tiles of one tile, and the longest item's entries (rings: of one of
+// its wavefronts).
+struct Items {
+  double count, slots, most, longest;
+};
+
+// A launch of independent items ends with the later of all its work and its
+// longest item, and somewhat later where both take as long.
+inline double either(double all, double longest, double p) {
+  const double m = std::max(all, longest);
+  return m * std::pow(std::pow(all / m, p) + std::pow(longest / m, p), 1.0 / p);
+}
+
+// The second launch, where tiles are split: all partial tiles, or one tile's
+// one after the other.
+inline double partials(const Items& it, double start, double slot, double chain) {
+  return it.slots > 0 ? start + std::max(slot * it.slots, chain * it.most) : 0.0;
+}
+
+// 0 .. 1: how much of the nodes' records (MB) lies beyond the caches.
+inline double beyond(const Nodes& n, double mb) {
+  const double r = n.nodes * (3 * n.width + 3) * 4e-6;
+  return r / (r + mb);
+}
+
+inline double gather(const Nodes& n, const Items& it) {
+  return 7.88 + either(2.89e-5 * n.entries + 0.00178 * it.count, 0.01415 * (1 + 1.01 * beyond(n, 4.51)) * it.longest, 4) +
+         partials(it, 1.05, 0.00655, 0.107);
+}
+inline double rings(const Nodes& n, const Items& it) {
+  return 8.6 + either(2.26e-5 * n.ring_entries + 7.31e-5 * n.rings + 0.008 * it.count, 0.0512 * it.longest, 10) +
+         partials(it, 1.51, 0.0084, 0.106);
+}
+// it: the items of the untuned gather, whose lists the tiles then shared
+inline double tiles(const Nodes& n, const Items& it) {
+  return 7.64 + either(1.76e-6 * n.entries * n.width + 0.00253 * it.count,
+                       0.00413 * (1 + 3.09 * beyond(n, 0.0107)) * it.longest, 5) +
+         std::max(2.3e-5 * n.nodes, 1.07e-5 * n.entries) + 0.152 * n.entries / n.nodes;
+}
+inline double staged(const Nodes& n, double count, double longest) {
+  return 8.2 + either(3.59e-5 * n.nodes * std::sqrt(n.width) + 0.0129 * count, 0.0268 * longest, 5);
+}
+
+// Ring items from which on the two longest chunks cost the same: with 21 254 of
+// them (256^3) they are 0.1 to 0.6% apart, and plans that timed them took
+// either, the shorter 30 times of 61 -- the one taken here.  With 17 722 (240^3)
+// the longer one was taken, 0.2 to 1.4% ahead.
+constexpr double kManyItems = 20000;
+
+}  // namespace formcost
+}  // namespace jgb

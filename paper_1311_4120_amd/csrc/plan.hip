@@ -13,6 +13,7 @@
 #include <thread>
 
 #include "common.h"
+#include "formcost.h"
 #include "lists.h"
 #include "radial.h"
 
@@ -511,30 +512,92 @@ Status time_stage(Plan& pl, bool interp, double& best_ms) {
   return Status::ok();
 }
 
-// What a tuned plan takes in JGB_MIXED.  There the form and the chunk of a sum
-// decide its last digits (E by some 1e-7), unlike in float64, and a program's
-// results should not move with the speed of a kernel or the noise of a timing.
-// They therefore follow the node count, the length of the tiles' lists and the
-// grid, along the lines where the staged interpolation and the tiles, the
-// gather and the rings, and one chunk and the next, were once measured equal
-// on 122 node sets.  (Today's tiles win between the lines too, by 15 to 50%: a
-// program that wants them asks for JGB_FLAG_INTERP_TILES.)
+// The forms of a tuned JGB_MIXED plan, from its work items and the costs of
+// formcost.h.
+formcost::Nodes form_nodes(const Plan& pl) {
+  return formcost::Nodes{(double)pl.Mh, (double)pl.width, (double)pl.nlist, (double)pl.nrnodes, (double)pl.nrings_ent};
+}
+
+// Partial tiles of a launch (multi: tile, first slot and slots of each split tile).
+void count_partials(const std::vector<int>& multi, int nslots, formcost::Items& it) {
+  it.slots = nslots;
+  for (size_t i = 2; i < multi.size(); i += 3) it.most = std::max(it.most, (double)multi[i]);
+}
+
+formcost::Items gather_shape(const Plan& pl, int chunk) {
+  std::vector<WorkItem> items;
+  std::vector<int> multi;
+  int nslots = 0;
+  spread_items(pl, chunk, items, multi, nslots);
+  formcost::Items it{};
+  for (const WorkItem& w : items) {
+    if (w.tile < 0) continue;
+    it.count += 1;
+    it.longest = std::max(it.longest, (double)(w.vend - w.vbegin));
+  }
+  count_partials(multi, nslots, it);
+  return it;
+}
+
+formcost::Items ring_shape(const Plan& pl, int chunk) {
+  std::vector<RingItem> items;
+  std::vector<int> multi;
+  int nslots = 0;
+  ring_items(pl, chunk, items, multi, nslots);
+  formcost::Items it{};
+  for (const RingItem& r : items) {
+    if (r.tile < 0) continue;
+    it.count += 1;
+    for (int w = 0; w < 4; ++w) it.longest = std::max(it.longest, (double)(r.e[w + 1] - r.e[w]));
+  }
+  count_partials(multi, nslots, it);
+  return it;
+}
+
+// Whether the interpolation takes the tiles (before the plan is tuned: the
+// gather's chunk is the untuned one).
 bool mixed_tiles(const Plan& pl) {
-  const int64_t points = (int64_t)pl.n[0] * pl.n[1] * pl.n[2];
-  return pl.split || pl.Mh <= 8000 || (pl.Mh <= 16000 && points <= 42000) || pl.Mh >= 500000 || pl.nlist >= 3360000;
+  const formcost::Nodes n = form_nodes(pl);
+  double best = 1e30;
+  for (int c : kInterpChunks) {
+    double count = 0, longest = 0;
+    for (const Plan::InterpItem& it : interp_items(pl, c)) {
+      count += it.end > it.begin;
+      longest = std::max(longest, (double)(it.end - it.begin));
+    }
+    best = std::min(best, formcost::staged(n, count, longest));
+  }
+  return formcost::tiles(n, gather_shape(pl, pl.spread_chunk)) < best;
 }
-bool mixed_rings(const Plan& pl) {
-  // a side that ends inside a ring tile costs the rings more than the gather,
-  // until the lists are long
-  const bool ragged = pl.nf[0] % kRingTile0 != 0;
-  return pl.Mh > kSmallNodeSet && !(ragged && pl.nlist >= 500000 && pl.nlist < 1400000);
-}
-int mixed_ring_chunk(const Plan& pl) {
-  return pl.Mh <= kSmallNodeSet ? 512 : pl.nlist < 1330000 ? 2048 : pl.nlist < 3360000 ? 4096 : pl.nlist < 10000000 ? 8192 : 16384;
-}
-int mixed_spread_chunk(const Plan& pl) {
-  const int c = pl.nlist < 170000 ? 256 : pl.Mh <= kSmallNodeSet ? 512 : 1024;
-  return std::max(c, min_spread_chunk(pl.Mh));
+
+// The spreading's chunk, negative for the rings.
+int mixed_spread(const Plan& pl, bool forced_rings) {
+  const formcost::Nodes n = form_nodes(pl);
+  int sc = 0;
+  double best = 1e30;
+  if (!forced_rings)
+    for (int c : kSpreadChunks) {
+      if (c < min_spread_chunk(pl.Mh)) continue;
+      const double t = formcost::gather(n, gather_shape(pl, c));
+      if (t < best) {
+        best = t;
+        sc = c;
+      }
+    }
+  double items = 0;
+  if (pl.ring_ok)
+    for (int c : kRingChunks) {
+      if (c < min_ring_chunk(pl.Mh)) continue;
+      if (c == 16384 && items >= formcost::kManyItems) continue;
+      const formcost::Items it = ring_shape(pl, c);
+      items = it.count;
+      const double t = formcost::rings(n, it);
+      if (t < best) {
+        best = t;
+        sc = -c;
+      }
+    }
+  return sc;
 }
 
 Status autotune(Plan& pl) {
@@ -556,6 +619,7 @@ Status autotune(Plan& pl) {
   size_t ngrid = (size_t)pl.nf[0] * pl.nf[1] * pl.nf[2];
   TRY_HIP(hipMemsetAsync(pl.d_F, 0, ngrid * 2 * pl.real_bytes, pl.stream), "autotune clear");
   double best_i = 1e30, best_s = 1e30;
+  const bool tiles = pl.tile_ok && !pl.fp64 && mixed_tiles(pl);
   for (int c : kInterpChunks) {
     TRY(apply_interp_chunk(pl, c));
     double ms;
@@ -567,8 +631,8 @@ Status autotune(Plan& pl) {
   }
   TRY(apply_interp_chunk(pl, ic));
   if (pl.tile_ok && !pl.fp64 && !forced) {
-    pl.tile_interp = mixed_tiles(pl);
-    if (pl.tile_interp) ic = kTileInterp;
+    pl.tile_interp = tiles;
+    if (tiles) ic = kTileInterp;
   } else if (pl.tile_ok && !forced) {
     // the interpolation by tiles on the matrix cores, against the best chunk
     pl.tile_interp = true;
@@ -582,8 +646,8 @@ Status autotune(Plan& pl) {
     }
   }
   if (!pl.fp64) {
-    pl.ring_spread = pl.ring_ok && (forced_rings || mixed_rings(pl));
-    sc = pl.ring_spread ? -mixed_ring_chunk(pl) : mixed_spread_chunk(pl);
+    sc = mixed_spread(pl, forced_rings);
+    pl.ring_spread = sc < 0;
     TRY(sc < 0 ? apply_ring_chunk(pl, -sc) : apply_spread_chunk(pl, sc));
     TRY(time_stage<float>(pl, true, best_i));  // node values for spreading
     TRY(time_stage<float>(pl, false, best_s));
