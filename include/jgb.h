@@ -99,7 +99,10 @@ typedef enum { JGB_THETA_GL = 0, JGB_COSTHETA_GL = 1 } jgb_theta_rule;
  * which moves no result by more than the rounding of E's float64 sum.  When the
  * environment variable JGB_AUTOTUNE_CACHE names a file, results are read from
  * and written to it (a JSON object keyed by grid, node counts, cutoff, width
- * and precision), so later plans of the same shape skip the timing. */
+ * and precision), so later plans of the same shape skip the timing.  An entry is
+ * taken as it stands, also in JGB_MIXED.  Plans with JGB_FLAG_INTERP_TILES or
+ * JGB_FLAG_SPREAD_RINGS write theirs under keys of their own, which other plans
+ * do not read. */
 #define JGB_FLAG_AUTOTUNE 1u
 /* Evaluate u by the partition-of-unity split of Algorithm 2 (Section 3.3,
  * eq. 3.9) instead of Algorithm 1.  A smooth window p (eq. 3.10 in 3D,

@@ -602,12 +602,17 @@ int mixed_spread(const Plan& pl, bool forced_rings) {
 
 Status autotune(Plan& pl) {
   const char* path = getenv("JGB_AUTOTUNE_CACHE");
-  const std::string key = tune_key(pl);
   int ic = 0, sc = 0;
   const bool forced = (pl.p.flags & JGB_FLAG_INTERP_TILES) != 0;
   const bool forced_rings = (pl.p.flags & JGB_FLAG_SPREAD_RINGS) != 0;
-  if (path && cache_lookup(path, key, ic, sc) && (ic != kTileInterp || pl.tile_ok) && (sc > 0 || pl.ring_ok) &&
-      !(forced_rings && sc > 0)) {
+  // a plan with a forced form keeps its choices under a key of its own, where
+  // plans without one do not find them, but takes theirs where it has none
+  const std::string shape = tune_key(pl), key = shape + (forced ? " tiles" : "") + (forced_rings ? " rings" : "");
+  auto lookup = [&](const std::string& k) {
+    return cache_lookup(path, k, ic, sc) && (ic != kTileInterp || pl.tile_ok) && (sc > 0 || pl.ring_ok) &&
+           !(forced_rings && sc > 0);
+  };
+  if (path && (lookup(key) || (key != shape && lookup(shape)))) {
     pl.tile_interp = forced || ic == kTileInterp;
     if (!pl.tile_interp) TRY(apply_interp_chunk(pl, ic));
     pl.ring_spread = sc < 0;
