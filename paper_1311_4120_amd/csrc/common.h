@@ -201,7 +201,7 @@ struct Plan {
   // index d_nstart / d_npos (node j's entries are d_npos[d_nstart[j] ..
   // d_nstart[j + 1])).
   // The work items are per wavefront, 8 kTileWaves of them to eight blocks.
-  bool tile_ok = false;        // the tables below are built (autotuned 3D plans)
+  bool tile_ok = false;        // the tables below are built (3D plans that take the tiles or, in float64, time them)
   int2* d_tlist = nullptr;     // the gather's lists, each tile's entries ordered by footprint
   int* d_tneed = nullptr;      // per 16 consecutive entries of a tile: bit x + 8 h if the footprint of one
                                // of them reaches the tile's points (x, y = 4h .. 4h + 3)

@@ -462,6 +462,21 @@ bool cache_lookup(const std::string& path, const std::string& key, int& ic, int&
   return ok_i && ok_s;
 }
 
+// The plan's entry of the tuning file, if it has one.  A plan with a forced form
+// keeps its choices under a key of its own, where plans without one do not find
+// them, but takes theirs where it has none.
+std::string own_tune_key(const Plan& pl) {
+  return tune_key(pl) + (pl.p.flags & JGB_FLAG_INTERP_TILES ? " tiles" : "") +
+         (pl.p.flags & JGB_FLAG_SPREAD_RINGS ? " rings" : "");
+}
+template <typename Fits>
+bool tuned_entry(const Plan& pl, int& ic, int& sc, Fits fits) {
+  const char* path = getenv("JGB_AUTOTUNE_CACHE");
+  if (!path) return false;
+  const std::string shape = tune_key(pl), own = own_tune_key(pl);
+  return (cache_lookup(path, own, ic, sc) && fits()) || (own != shape && cache_lookup(path, shape, ic, sc) && fits());
+}
+
 void cache_store(const std::string& path, const std::string& key, int ic, int sc, double ms_i, double ms_s) {
   std::string text;
   if (FILE* f = fopen(path.c_str(), "r")) {
@@ -605,14 +620,10 @@ Status autotune(Plan& pl) {
   int ic = 0, sc = 0;
   const bool forced = (pl.p.flags & JGB_FLAG_INTERP_TILES) != 0;
   const bool forced_rings = (pl.p.flags & JGB_FLAG_SPREAD_RINGS) != 0;
-  // a plan with a forced form keeps its choices under a key of its own, where
-  // plans without one do not find them, but takes theirs where it has none
-  const std::string shape = tune_key(pl), key = shape + (forced ? " tiles" : "") + (forced_rings ? " rings" : "");
-  auto lookup = [&](const std::string& k) {
-    return cache_lookup(path, k, ic, sc) && (ic != kTileInterp || pl.tile_ok) && (sc > 0 || pl.ring_ok) &&
-           !(forced_rings && sc > 0);
-  };
-  if (path && (lookup(key) || (key != shape && lookup(shape)))) {
+  const std::string key = own_tune_key(pl);
+  if (tuned_entry(pl, ic, sc, [&] {
+        return (ic != kTileInterp || pl.tile_ok) && (sc > 0 || pl.ring_ok) && !(forced_rings && sc > 0);
+      })) {
     pl.tile_interp = forced || ic == kTileInterp;
     if (!pl.tile_interp) TRY(apply_interp_chunk(pl, ic));
     pl.ring_spread = sc < 0;
@@ -624,21 +635,34 @@ Status autotune(Plan& pl) {
   size_t ngrid = (size_t)pl.nf[0] * pl.nf[1] * pl.nf[2];
   TRY_HIP(hipMemsetAsync(pl.d_F, 0, ngrid * 2 * pl.real_bytes, pl.stream), "autotune clear");
   double best_i = 1e30, best_s = 1e30;
-  const bool tiles = pl.tile_ok && !pl.fp64 && mixed_tiles(pl);
-  for (int c : kInterpChunks) {
-    TRY(apply_interp_chunk(pl, c));
-    double ms;
-    TRY(pl.fp64 ? time_stage<double>(pl, true, ms) : time_stage<float>(pl, true, ms));
-    if (ms < best_i) {
-      best_i = ms;
-      ic = c;
+  const bool tiles = !pl.fp64 && pl.tile_ok && (forced || mixed_tiles(pl));
+  if (tiles) {
+    pl.tile_interp = true;
+    ic = kTileInterp;
+  } else {
+    for (int c : kInterpChunks) {
+      TRY(apply_interp_chunk(pl, c));
+      double ms;
+      TRY(pl.fp64 ? time_stage<double>(pl, true, ms) : time_stage<float>(pl, true, ms));
+      if (ms < best_i) {
+        best_i = ms;
+        ic = c;
+      }
     }
+    TRY(apply_interp_chunk(pl, ic));
   }
-  TRY(apply_interp_chunk(pl, ic));
-  if (pl.tile_ok && !pl.fp64 && !forced) {
-    pl.tile_interp = tiles;
-    if (tiles) ic = kTileInterp;
-  } else if (pl.tile_ok && !forced) {
+  if (!pl.fp64) {
+    sc = mixed_spread(pl, forced_rings);
+    pl.ring_spread = sc < 0;
+    TRY(sc < 0 ? apply_ring_chunk(pl, -sc) : apply_spread_chunk(pl, sc));
+    if (path) {
+      TRY(time_stage<float>(pl, true, best_i));  // node values for spreading
+      TRY(time_stage<float>(pl, false, best_s));
+      cache_store(path, key, ic, sc, best_i, best_s);
+    }
+    return Status::ok();
+  }
+  if (pl.tile_ok && !forced) {
     // the interpolation by tiles on the matrix cores, against the best chunk
     pl.tile_interp = true;
     double ms;
@@ -649,15 +673,6 @@ Status autotune(Plan& pl) {
     } else {
       pl.tile_interp = false;
     }
-  }
-  if (!pl.fp64) {
-    sc = mixed_spread(pl, forced_rings);
-    pl.ring_spread = sc < 0;
-    TRY(sc < 0 ? apply_ring_chunk(pl, -sc) : apply_spread_chunk(pl, sc));
-    TRY(time_stage<float>(pl, true, best_i));  // node values for spreading
-    TRY(time_stage<float>(pl, false, best_s));
-    if (path) cache_store(path, key, ic, sc, best_i, best_s);
-    return Status::ok();
   }
   double ms0;
   TRY(time_stage<double>(pl, true, ms0));  // node values for spreading
@@ -1053,8 +1068,7 @@ Status build_plan(Plan& pl, const jgb_params* p) {
   pl.gather_nowrap = true;
   for (int a = 0; a < 3; ++a) pl.gather_nowrap &= pl.nf[a] >= pl.GT[a] + pl.w[a] - 1;
   // the node-major index of the list, for the tile interpolation (built only
-  // for autotuned plans: the tuner times it against the staged interpolation
-  // and keeps the faster)
+  // for plans that take it and, in float64, those that time it)
   pl.tile_ok = pl.dim == 3 && pl.GT[0] == 8 && pl.GT[1] == 8 && pl.GT[2] == 8 &&
                (p->flags & (JGB_FLAG_AUTOTUNE | JGB_FLAG_INTERP_TILES));
   pl.tile_interp = pl.tile_ok && (p->flags & JGB_FLAG_INTERP_TILES);
@@ -1075,6 +1089,24 @@ Status build_plan(Plan& pl, const jgb_params* p) {
     if (!err.empty()) return fail(JGB_ERR_UNSUPPORTED, err);
   }
   const int64_t nlist = tcount[pl.ngtiles];
+  pl.nlist = nlist;
+  pl.h_tcount = tcount;
+  {
+    // the untuned chunk, as above
+    std::vector<WorkItem> items;
+    std::vector<int> multi;
+    int nslots = 0;
+    while (pl.spread_chunk > min_spread_chunk(pl.Mh)) {
+      spread_items(pl, pl.spread_chunk, items, multi, nslots);
+      if ((int)items.size() >= fill_items) break;
+      pl.spread_chunk /= 2;
+    }
+  }
+  if (pl.tile_ok && !pl.fp64 && !(p->flags & JGB_FLAG_INTERP_TILES)) {
+    // no tables for a form that the plan will not take
+    int ic = 0, sc = 0;
+    pl.tile_ok = tuned_entry(pl, ic, sc, [&] { return ic == kTileInterp; }) || mixed_tiles(pl);
+  }
   if (pl.tile_ok) {
     // the interpolation's own order of each tile's list
     const std::unique_ptr<lists::Entry[]> tlist(new lists::Entry[std::max<int64_t>(nlist, 1)]);
@@ -1093,9 +1125,6 @@ Status build_plan(Plan& pl, const jgb_params* p) {
   }
   TRY(dev_alloc(pl, &pl.d_list, sizeof(lists::Entry) * list.size()));
   TRY(upload(pl, pl.d_list, list.data(), sizeof(lists::Entry) * list.size()));
-  pl.nlist = nlist;
-
-  pl.h_tcount = tcount;
   if (pl.tile_ok) {
     const std::vector<TileItem> ti = tile_items(pl, tgroup);
     TRY(dev_alloc(pl, &pl.d_titems, sizeof(TileItem) * std::max<size_t>(ti.size(), 1)));
@@ -1153,11 +1182,6 @@ Status build_plan(Plan& pl, const jgb_params* p) {
       pl.items_cap = std::max(pl.items_cap, (int)items.size());
       pl.multi_cap = std::max(pl.multi_cap, (int)multi.size());
       pl.slots_cap = std::max(pl.slots_cap, nslots);
-    }
-    while (pl.spread_chunk > min_spread_chunk(pl.Mh)) {
-      spread_items(pl, pl.spread_chunk, items, multi, nslots);
-      if ((int)items.size() >= fill_items) break;
-      pl.spread_chunk /= 2;
     }
     TRY(dev_alloc(pl, &pl.d_items, sizeof(WorkItem) * std::max(pl.items_cap, 1)));
     TRY(dev_alloc(pl, &pl.d_multi, sizeof(int) * std::max(pl.multi_cap, 1)));

@@ -49,3 +49,22 @@ def test_form(n, nodes, eps, split, tiles, chunk, monkeypatch):
     plan.close()
     print("mixed form", n, nodes, eps, split, got, flush=True)
     assert got == (tiles, chunk)
+
+
+@pytest.mark.parametrize("n,nodes,tiles", [((64, 64, 64), (64, 32, 64), False), ((96, 96, 96), (76, 38, 76), False),
+                                           ((32, 32, 32), (32, 16, 32), True)])
+def test_no_tables_for_a_refused_form(n, nodes, tiles, monkeypatch):
+    """Tuning a mixed plan that keeps the staged interpolation costs no device
+    memory: the plan holds what the same plan untuned does (with the ring
+    tables, which the choice of the spreading needs)."""
+    import paper_1311_4120_amd as jgb
+    monkeypatch.delenv("JGB_AUTOTUNE_CACHE", raising=False)
+    kw = dict(eps=1e-5, precision="mixed", axis=(0.48, 0.6, 0.64), spread_rings=True)
+    box = tuple(0.15 * v for v in n)
+    plain, tuned = jgb.Plan(n, box, "dipole3d", nodes, **kw), jgb.Plan(n, box, "dipole3d", nodes, autotune=True, **kw)
+    got = [p.info["workspace_bytes"] for p in (plain, tuned)]
+    form = tuned.info["interp_chunk"] == 0
+    plain.close()
+    tuned.close()
+    print("tables", n, nodes, got, flush=True)
+    assert form == tiles and (got[1] > got[0] if tiles else got[1] == got[0])
