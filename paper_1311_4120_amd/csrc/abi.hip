@@ -418,8 +418,9 @@ static jgb_status bind_batched(jgb_batch_s* b, const void* const* rho, void* con
     for (auto& g : groups) std::sort(g.begin(), g.end());
   }
   struct Site {
-    jgb::BatchLaunch f;
+    jgb::BatchLaunch key;  // what its launches share: `any` where they have one
     int occ;
+    jgb::BatchLaunch f;    // the members' own form if it is the same, else key
     std::vector<std::pair<int, int>> members;  // (member, record)
     size_t toff = 0, boff = 0;
     unsigned blocks = 0, threads = 0;
@@ -434,20 +435,21 @@ static jgb_status bind_batched(jgb_batch_s* b, const void* const* rho, void* con
       std::vector<std::pair<jgb::BatchLaunch, int>> seen;
       int prev = -1;
       for (int r = 0; r < (int)recs[i].size(); ++r) {
-        const jgb::BatchLaunch f = recs[i][r].launch;
+        const jgb::BatchLaunch f = recs[i][r].launch, key = recs[i][r].any ? recs[i][r].any : f;
         int occ = 0;
         for (auto& q : seen)
-          if (q.first == f) occ = ++q.second;
-        if (occ == 0) seen.push_back({f, 0});
+          if (q.first == key) occ = ++q.second;
+        if (occ == 0) seen.push_back({key, 0});
         int pos = -1;
         for (int k = 0; k < (int)sites.size(); ++k)
-          if (sites[k].f == f && sites[k].occ == occ) pos = k;
+          if (sites[k].key == key && sites[k].occ == occ) pos = k;
         if (pos < 0) {
           pos = prev + 1;
-          sites.insert(sites.begin() + pos, Site{f, occ, {}});
+          sites.insert(sites.begin() + pos, Site{key, occ, f, {}});
         } else if (pos <= prev) {
           return report(JGB_ERR_UNSUPPORTED, "batch members' pipelines do not merge");
         }
+        if (sites[pos].f != f) sites[pos].f = key;
         sites[pos].members.push_back({i, r});
         prev = pos;
       }

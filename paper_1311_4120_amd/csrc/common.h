@@ -338,6 +338,9 @@ typedef hipError_t (*BatchLaunch)(const void* table, const int* bstart, int nmem
                                   unsigned threads, size_t smem, hipStream_t s);
 struct LaunchRecord {
   BatchLaunch launch;
+  // where launches of one site of the pipeline have batched forms of their own:
+  // the form that runs them all, for batches whose members differ in theirs
+  BatchLaunch any = nullptr;
   std::vector<unsigned char> args;  // the kernel's argument block
   unsigned blocks = 0, threads = 0;
   size_t smem = 0;
@@ -373,11 +376,13 @@ hipError_t batch_launch(const void* table, const int* bstart, int nm, unsigned b
 // With a record open, append a launch (argument block a, its batched form, and
 // that form's block size and LDS) and return true.
 template <typename A>
-bool launch_recorded(const A& a, BatchLaunch batched, unsigned blocks, unsigned threads, size_t smem) {
+bool launch_recorded(const A& a, BatchLaunch batched, unsigned blocks, unsigned threads, size_t smem,
+                     BatchLaunch any = nullptr) {
   std::vector<LaunchRecord>* rec = launch_record();
   if (!rec) return false;
   LaunchRecord r;
   r.launch = batched;
+  r.any = any;
   r.args.assign(reinterpret_cast<const unsigned char*>(&a), reinterpret_cast<const unsigned char*>(&a) + sizeof(A));
   r.blocks = blocks;
   r.threads = threads;
@@ -387,10 +392,10 @@ bool launch_recorded(const A& a, BatchLaunch batched, unsigned blocks, unsigned 
 }
 
 // Launch kernel K (argument block a) or, with a record open, record it with
-// its batched form KB.
+// its batched form KB (and the form that runs other launches of its site too).
 template <typename A, void (*K)(A), void (*KB)(const A*, const int*, int)>
-hipError_t launch(const A& a, unsigned blocks, unsigned threads, size_t smem, hipStream_t s) {
-  if (launch_recorded(a, &batch_launch<A, KB>, blocks, threads, smem)) return hipSuccess;
+hipError_t launch(const A& a, unsigned blocks, unsigned threads, size_t smem, hipStream_t s, BatchLaunch any = nullptr) {
+  if (launch_recorded(a, &batch_launch<A, KB>, blocks, threads, smem, any)) return hipSuccess;
   if (blocks == 0) return hipSuccess;
   hipLaunchKernelGGL(K, dim3(blocks), dim3(threads), smem, s, a);
   return hipGetLastError();
