@@ -223,9 +223,18 @@ inline void order_tiles(const Geometry& g, bool nowrap, int bias, const std::vec
     }
     return c * nx + ex;
   };
-  parallel_ranges(ntiles, threads, [&](int64_t b, int64_t e, int) {
-    std::vector<int64_t> at(3 * nx + 1);
-    for (int64_t tile = b; tile < e; ++tile) {
+  // threads over runs of tiles with about equally many entries (the lists near
+  // k = 0 are a thousand times the median); nothing is allocated on a thread,
+  // where a failure could not be reported
+  threads = usable_threads(threads, nlist, 3 * nx + 1);
+  std::vector<std::vector<int64_t>> starts(threads, std::vector<int64_t>(3 * nx + 1));
+  auto first = [&](int64_t t) {
+    return std::lower_bound(tcount.begin(), tcount.end() - 1, nlist * t / threads) - tcount.begin();
+  };
+  parallel_ranges(threads, threads, [&](int64_t t, int64_t, int) {
+    std::vector<int64_t>& at = starts[t];
+    const int64_t end = t + 1 < threads ? first(t + 1) : ntiles;
+    for (int64_t tile = first(t); tile < end; ++tile) {
       std::fill(at.begin(), at.end(), 0);
       for (int64_t i = tcount[tile]; i < tcount[tile + 1]; ++i) at[key(list[i]) + 1]++;
       for (int k = 0; k < 3 * nx; ++k) at[k + 1] += at[k];
