@@ -219,8 +219,9 @@ std::vector<Plan::InterpItem> interp_items(const Plan& pl, int chunk) {
 }
 
 // Gather work items: one block per tile, tiles with longer lists split into
-// chunks whose partial tiles are summed afterwards.
-void spread_items(const Plan& pl, int chunk, std::vector<WorkItem>& items, std::vector<int>& multi, int& nslots) {
+// chunks whose partial tiles are summed afterwards.  (`cut`: in tile order, not
+// yet in that of their dispatch.)
+void cut_gather(const Plan& pl, int chunk, std::vector<WorkItem>& items, std::vector<int>& multi, int& nslots) {
   items.clear();
   multi.clear();
   nslots = 0;
@@ -243,6 +244,9 @@ void spread_items(const Plan& pl, int chunk, std::vector<WorkItem>& items, std::
       nslots += k;
     }
   }
+}
+void spread_items(const Plan& pl, int chunk, std::vector<WorkItem>& items, std::vector<int>& multi, int& nslots) {
+  cut_gather(pl, chunk, items, multi, nslots);
   const int n12 = pl.gnt[1] * pl.gnt[2];
   auto key = [&](const WorkItem& it) {
     const int t0 = it.tile / n12, r = it.tile - t0 * n12, t1 = r / pl.gnt[2], t2 = r - t1 * pl.gnt[2];
@@ -282,7 +286,7 @@ std::vector<TileItem> tile_items(const Plan& pl, const std::vector<int64_t>& tgr
 // partial tiles (cost: node entries plus kRingEntryCost per ring); each item's
 // rings are shared out among the block's four wavefronts in contiguous runs
 // of about equal cost.
-void ring_items(const Plan& pl, int chunk, std::vector<RingItem>& items, std::vector<int>& multi, int& nslots) {
+void cut_rings(const Plan& pl, int chunk, std::vector<RingItem>& items, std::vector<int>& multi, int& nslots) {
   items.clear();
   multi.clear();
   nslots = 0;
@@ -323,6 +327,9 @@ void ring_items(const Plan& pl, int chunk, std::vector<RingItem>& items, std::ve
     multi.push_back(first);
     multi.push_back(nslots - first);
   }
+}
+void ring_items(const Plan& pl, int chunk, std::vector<RingItem>& items, std::vector<int>& multi, int& nslots) {
+  cut_rings(pl, chunk, items, multi, nslots);
   const int n12 = pl.rnt[1] * pl.rnt[2];
   auto key = [&](const RingItem& it) {
     const int t0 = it.tile / n12, r = it.tile - t0 * n12, t1 = r / pl.rnt[2], t2 = r - t1 * pl.rnt[2];
@@ -543,13 +550,10 @@ formcost::Items gather_shape(const Plan& pl, int chunk) {
   std::vector<WorkItem> items;
   std::vector<int> multi;
   int nslots = 0;
-  spread_items(pl, chunk, items, multi, nslots);
+  cut_gather(pl, chunk, items, multi, nslots);
   formcost::Items it{};
-  for (const WorkItem& w : items) {
-    if (w.tile < 0) continue;
-    it.count += 1;
-    it.longest = std::max(it.longest, (double)(w.vend - w.vbegin));
-  }
+  it.count = (double)items.size();
+  for (const WorkItem& w : items) it.longest = std::max(it.longest, (double)(w.vend - w.vbegin));
   count_partials(multi, nslots, it);
   return it;
 }
@@ -558,13 +562,11 @@ formcost::Items ring_shape(const Plan& pl, int chunk) {
   std::vector<RingItem> items;
   std::vector<int> multi;
   int nslots = 0;
-  ring_items(pl, chunk, items, multi, nslots);
+  cut_rings(pl, chunk, items, multi, nslots);
   formcost::Items it{};
-  for (const RingItem& r : items) {
-    if (r.tile < 0) continue;
-    it.count += 1;
+  it.count = (double)items.size();
+  for (const RingItem& r : items)
     for (int w = 0; w < 4; ++w) it.longest = std::max(it.longest, (double)(r.e[w + 1] - r.e[w]));
-  }
   count_partials(multi, nslots, it);
   return it;
 }
@@ -575,10 +577,11 @@ bool mixed_tiles(const Plan& pl) {
   const formcost::Nodes n = form_nodes(pl);
   double best = 1e30;
   for (int c : kInterpChunks) {
-    double count = 0, longest = 0;
-    for (const Plan::InterpItem& it : interp_items(pl, c)) {
-      count += it.end > it.begin;
-      longest = std::max(longest, (double)(it.end - it.begin));
+    int64_t count = 0, longest = 0;
+    for (size_t k = 0; k + 1 < pl.h_sub_start.size(); ++k) {
+      const int64_t m = pl.h_sub_start[k + 1] - pl.h_sub_start[k];
+      count += (m + c - 1) / c;
+      longest = std::max(longest, std::min<int64_t>(m, c));
     }
     best = std::min(best, formcost::staged(n, count, longest));
   }
