@@ -46,9 +46,6 @@ constexpr int kRingTile2 = 16;
 // each): the entry is its ring's last in the tile, and then the a2 start code.
 constexpr int kRingEndBit = 20;
 constexpr int kRingZBit = 21;
-// Spare entries at the end of the ring node list (read by the prefetch of the
-// batch after the last).
-constexpr int kRingSpare = 32;
 // Per-node kernel values, tabulated at plan time: for each internal axis a,
 // the w values of its taps at [a (w + 1), a (w + 1) + w) of the node's record
 // followed by a zero (a unit axis has the single value 1 at tap 0 and zeros
@@ -214,10 +211,9 @@ struct Plan {
   // lists, ring by ring, the ring's nodes that touch the tile (d_rnodes: node
   // and code = a0 start | a1 start << 10, each ring padded to whole groups of
   // four with entries whose a0 values all vanish; the ring's last entry also
-  // carries kRingEndBit and its a2 start at kRingZBit; kRingSpare spare
-  // entries at the end).  Work items run over ranges of a tile's entries that
-  // hold whole rings; split tiles write partial tiles (d_partials) that
-  // d_rmulti sums.  The host keeps per tile its ring ranges (h_rcount into
+  // carries kRingEndBit and its a2 start at kRingZBit).  Work items run over
+  // ranges of a tile's entries that hold whole rings; split tiles write partial
+  // tiles (d_partials) that d_rmulti sums.  The host keeps per tile its ring ranges (h_rcount into
   // h_rcost, each ring's entry count, h_rfirst its first entry).
   bool ring_ok = false;        // the ring tables are built
   bool ring_spread = false;    // and the spreading uses them

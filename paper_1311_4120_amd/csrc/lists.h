@@ -343,7 +343,7 @@ inline std::string ring_lists(const Geometry& g, int bias, int nph2, int nrings,
     tring[t + 1] += tring[t];
   }
   if (tsize[ntiles] + spare >= ((int64_t)1 << 31)) return "ring node lists too long";
-  rnodes.assign(tsize[ntiles] + spare, Entry{0, kPad});  // the spare entries are read by the last prefetch
+  rnodes.assign(tsize[ntiles] + spare, Entry{0, kPad});
   rcost.assign(tring[ntiles], 0);
   rfirst.assign(tring[ntiles], 0);
   rcount = tring;

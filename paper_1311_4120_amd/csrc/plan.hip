@@ -378,7 +378,7 @@ Status build_ring_lists(Plan& pl, const std::vector<int>& perm, const std::vecto
   pl.nrtiles = pl.rnt[0] * pl.rnt[1] * pl.rnt[2];
   std::vector<lists::Entry> rnodes;
   const std::string err = lists::ring_lists(g, kGatherBias, pl.n_phi / 2, pl.n_r * pl.n_theta, perm, hdr, kRingEndBit,
-                                            kRingZBit, kRingSpare, rnodes, pl.h_rcount, pl.h_rcost, pl.h_rfirst,
+                                            kRingZBit, /*spare=*/0, rnodes, pl.h_rcount, pl.h_rcost, pl.h_rfirst,
                                             host_threads());
   if (!err.empty()) return fail(JGB_ERR_UNSUPPORTED, err);
   pl.nrings_ent = (int64_t)pl.h_rcost.size();
