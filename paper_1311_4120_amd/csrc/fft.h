@@ -13,17 +13,31 @@ struct alignas(2 * sizeof(T)) C2 {  // one 16-byte (fp64) or 8-byte (fp32) acces
   T x, y;
 };
 
+// The arithmetic of the passes, with every rounding written out: which product
+// of a sum goes into a fused multiply-add is the compiler's choice otherwise,
+// and may differ from one kernel that holds a butterfly to the next -- a batch
+// runs the passes from other kernels than a plan, with the same bits.
+#pragma clang fp contract(off)
+
+__device__ __forceinline__ double fma_(double a, double b, double c) { return __builtin_fma(a, b, c); }
+__device__ __forceinline__ float fma_(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+
 template <typename T>
-__device__ inline C2<T> cadd(C2<T> a, C2<T> b) { return {a.x + b.x, a.y + b.y}; }
+__device__ __forceinline__ C2<T> cadd(C2<T> a, C2<T> b) { return {a.x + b.x, a.y + b.y}; }
 template <typename T>
-__device__ inline C2<T> csub(C2<T> a, C2<T> b) { return {a.x - b.x, a.y - b.y}; }
+__device__ __forceinline__ C2<T> csub(C2<T> a, C2<T> b) { return {a.x - b.x, a.y - b.y}; }
 template <typename T>
-__device__ inline C2<T> cmul(C2<T> a, C2<T> b) { return {a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x}; }
-// multiply by i * s (s = +-1)
+__device__ __forceinline__ C2<T> cmul(C2<T> a, C2<T> b) {
+  return {fma_(a.x, b.x, -(a.y * b.y)), fma_(a.y, b.x, a.x * b.y)};
+}
+// a + r b (r real)
 template <typename T>
-__device__ inline C2<T> cmul_is(C2<T> a, T s) { return {-s * a.y, s * a.x}; }
+__device__ __forceinline__ C2<T> cfma(T r, C2<T> b, C2<T> a) { return {fma_(r, b.x, a.x), fma_(r, b.y, a.y)}; }
+// a + i r b
 template <typename T>
-__device__ inline C2<T> cscale(C2<T> a, T s) { return {a.x * s, a.y * s}; }
+__device__ __forceinline__ C2<T> cfma_i(T r, C2<T> b, C2<T> a) { return {fma_(-r, b.y, a.x), fma_(r, b.x, a.y)}; }
+
+#pragma clang fp contract(fast)
 
 // FWD_Z / INV_Z: the oversampled grid's first and last passes (real in or out,
 // deconvolution factors); COMPLEX: a complex pass along a strided axis;
@@ -111,7 +125,9 @@ struct PassArgs {
 // periodic passes: the line length, its radices and every extent are run-time
 // values, and the line stays in LDS from load to store.
 
-// In-register DFTs of small radix, y_k = sum_n x_n exp(s 2 pi i n k / R).
+#pragma clang fp contract(off)
+
+// In-register DFTs of small radix, y_k = sum_n x_n exp(s 2 pi i n k / R), s = +-1.
 template <typename T>
 __device__ inline void dft2(C2<T>* v, T) {
   C2<T> a = v[0], b = v[1];
@@ -123,22 +139,20 @@ template <typename T>
 __device__ inline void dft4(C2<T>* v, T s) {
   C2<T> a = cadd(v[0], v[2]), b = csub(v[0], v[2]);
   C2<T> c = cadd(v[1], v[3]), d = csub(v[1], v[3]);
-  C2<T> isd = cmul_is(d, s);
   v[0] = cadd(a, c);
   v[2] = csub(a, c);
-  v[1] = cadd(b, isd);
-  v[3] = csub(b, isd);
+  v[1] = cfma_i(s, d, b);
+  v[3] = cfma_i(-s, d, b);
 }
 
 template <typename T>
 __device__ inline void dft3(C2<T>* v, T s) {
-  const T h = T(0.86602540378443864676);  // sin(2 pi / 3)
-  C2<T> t = cadd(v[1], v[2]);
-  C2<T> m = {v[0].x - T(0.5) * t.x, v[0].y - T(0.5) * t.y};
-  C2<T> d = cmul_is(csub(v[1], v[2]), s * h);
+  const T h = s * T(0.86602540378443864676);  // sin(2 pi / 3)
+  C2<T> t = cadd(v[1], v[2]), d = csub(v[1], v[2]);
+  C2<T> m = cfma(T(-0.5), t, v[0]);
   v[0] = cadd(v[0], t);
-  v[1] = cadd(m, d);
-  v[2] = csub(m, d);
+  v[1] = cfma_i(h, d, m);
+  v[2] = cfma_i(-h, d, m);
 }
 
 template <typename T>
@@ -148,16 +162,15 @@ __device__ inline void dft5(C2<T>* v, T s) {
   C2<T> a1 = cadd(v[1], v[4]), b1 = csub(v[1], v[4]);
   C2<T> a2 = cadd(v[2], v[3]), b2 = csub(v[2], v[3]);
   C2<T> x0 = v[0];
-  C2<T> r1 = {x0.x + c1 * a1.x + c2 * a2.x, x0.y + c1 * a1.y + c2 * a2.y};
-  C2<T> r2 = {x0.x + c2 * a1.x + c1 * a2.x, x0.y + c2 * a1.y + c1 * a2.y};
-  C2<T> q1 = {s1 * b1.x + s2 * b2.x, s1 * b1.y + s2 * b2.y};
-  C2<T> q2 = {s2 * b1.x - s1 * b2.x, s2 * b1.y - s1 * b2.y};
-  C2<T> iq1 = cmul_is(q1, s), iq2 = cmul_is(q2, s);
+  C2<T> r1 = cfma(c2, a2, cfma(c1, a1, x0));
+  C2<T> r2 = cfma(c1, a2, cfma(c2, a1, x0));
+  C2<T> q1 = {fma_(s2, b2.x, s1 * b1.x), fma_(s2, b2.y, s1 * b1.y)};
+  C2<T> q2 = {fma_(s2, b1.x, -(s1 * b2.x)), fma_(s2, b1.y, -(s1 * b2.y))};
   v[0] = cadd(x0, cadd(a1, a2));
-  v[1] = cadd(r1, iq1);
-  v[4] = csub(r1, iq1);
-  v[2] = cadd(r2, iq2);
-  v[3] = csub(r2, iq2);
+  v[1] = cfma_i(s, q1, r1);
+  v[4] = cfma_i(-s, q1, r1);
+  v[2] = cfma_i(s, q2, r2);
+  v[3] = cfma_i(-s, q2, r2);
 }
 
 template <typename T>
@@ -168,21 +181,23 @@ __device__ inline void dft8(C2<T>* v, T s) {
   dft4(e, s);
   dft4(o, s);
   // twiddles w^k, w = exp(s 2 pi i / 8)
-  C2<T> o1 = {r * (o[1].x - s * o[1].y), r * (o[1].y + s * o[1].x)};
-  C2<T> o2 = cmul_is(o[2], s);
-  C2<T> o3 = {r * (-o[3].x - s * o[3].y), r * (-o[3].y + s * o[3].x)};
+  const C2<T> t1 = cfma_i(s, o[1], o[1]), t3 = cfma_i(s, o[3], C2<T>{-o[3].x, -o[3].y});
   v[0] = cadd(e[0], o[0]);
   v[4] = csub(e[0], o[0]);
-  v[1] = cadd(e[1], o1);
-  v[5] = csub(e[1], o1);
-  v[2] = cadd(e[2], o2);
-  v[6] = csub(e[2], o2);
-  v[3] = cadd(e[3], o3);
-  v[7] = csub(e[3], o3);
+  v[1] = cfma(r, t1, e[1]);
+  v[5] = cfma(-r, t1, e[1]);
+  v[2] = cfma_i(s, o[2], e[2]);
+  v[6] = cfma_i(-s, o[2], e[2]);
+  v[3] = cfma(r, t3, e[3]);
+  v[7] = cfma(-r, t3, e[3]);
 }
+
+#pragma clang fp contract(fast)
 
 // Radix 16 as 4 x 4: with n = 4 n1 + n2 and k = k1 + 4 k2,
 // y_k = sum_n2 w16^(n2 k1) [sum_n1 x_(4 n1 + n2) w4^(n1 k1)] w4^(n2 k2).
+// Only the float32 paired passes use it, which no batch runs: its products'
+// roundings are the compiler's.
 template <typename T>
 __device__ inline void dft16(C2<T>* v, T s) {
   const T c1 = T(0.92387953251128675613), s1 = T(0.38268343236508977173);  // cos, sin of pi/8
@@ -196,16 +211,17 @@ __device__ inline void dft16(C2<T>* v, T s) {
     for (int k1 = 0; k1 < 4; ++k1) a[n2][k1] = t[k1];
   }
   // twiddles w16^m = (cos(2 pi m / 16), s sin(2 pi m / 16)) for m = n2 k1
+  auto mul = [](C2<T> a, C2<T> b) { return C2<T>{a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x}; };
   const C2<T> w1{c1, s * s1}, w2{r, s * r}, w3{s1, s * c1}, w6{-r, s * r}, w9{-c1, -s * s1};
-  a[1][1] = cmul(a[1][1], w1);
-  a[1][2] = cmul(a[1][2], w2);
-  a[1][3] = cmul(a[1][3], w3);
-  a[2][1] = cmul(a[2][1], w2);
-  a[2][2] = cmul_is(a[2][2], s);
-  a[2][3] = cmul(a[2][3], w6);
-  a[3][1] = cmul(a[3][1], w3);
-  a[3][2] = cmul(a[3][2], w6);
-  a[3][3] = cmul(a[3][3], w9);
+  a[1][1] = mul(a[1][1], w1);
+  a[1][2] = mul(a[1][2], w2);
+  a[1][3] = mul(a[1][3], w3);
+  a[2][1] = mul(a[2][1], w2);
+  a[2][2] = C2<T>{-s * a[2][2].y, s * a[2][2].x};
+  a[2][3] = mul(a[2][3], w6);
+  a[3][1] = mul(a[3][1], w3);
+  a[3][2] = mul(a[3][2], w6);
+  a[3][3] = mul(a[3][3], w9);
 #pragma unroll
   for (int k1 = 0; k1 < 4; ++k1) {
     C2<T> t[4] = {a[0][k1], a[1][k1], a[2][k1], a[3][k1]};
@@ -594,10 +610,10 @@ __device__ __forceinline__ void fft_pass_body(const PassArgs<T>& a, const int bl
         if (dp > ox.y) continue;  // never read: not stored
       }
       if constexpr (KIND == PASS_INV_Z) {
-        double u = (double)buf[i].x * (fline[l] * felem[e]) + ushift;
+        double u = __builtin_fma((double)buf[i].x, fline[l] * felem[e], ushift);
         if (a.split) u += (double)buf[i].y;
         ((T*)a.out)[base] = (T)u;
-        eacc += (double)rho_v[i] * u;
+        eacc = __builtin_fma((double)rho_v[i], u, eacc);
       } else {
         ((C2<T>*)a.out)[base] = buf[i];
       }

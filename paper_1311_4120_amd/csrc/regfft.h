@@ -16,8 +16,10 @@
 // (q / Ns) Ns R + q mod Ns + r Ns.
 //
 // float64 uses large radices (fewer exchanges), float32 the radix sequence and
-// butterflies of the any-length kernel (fft.h): the results of a length are the
-// same bits whichever of the two kernels runs it.
+// butterflies of the any-length kernel (fft.h): the digits of a mixed plan's
+// results are those of that kernel (u has the same bits as where it runs every
+// length on 288 3D and 192 planar grids with sides of 8 to 512 points).  Both
+// write every rounding out, so that a kernel's batched form gives its bits too.
 #pragma once
 
 #include "fft.h"
@@ -73,6 +75,8 @@ struct Root {
   static constexpr double c = cos720(t), s = cos720(t + 540);
 };
 
+#pragma clang fp contract(off)  // every rounding written out (fft.h)
+
 // a exp(SG 2 pi i K / N)
 template <int SG, int K, int N, typename T>
 __device__ __forceinline__ C2<T> rot(C2<T> a) {
@@ -83,7 +87,7 @@ __device__ __forceinline__ C2<T> rot(C2<T> a) {
   else if constexpr (t == 540) return C2<T>{a.y, -a.x};
   else {
     constexpr T c = (T)Root<SG * K, N>::c, s = (T)Root<SG * K, N>::s;
-    return C2<T>{a.x * c - a.y * s, a.x * s + a.y * c};
+    return C2<T>{fma_(a.x, c, -(a.y * s)), fma_(a.x, s, a.y * c)};
   }
 }
 
@@ -97,10 +101,10 @@ __device__ __forceinline__ void rdft(C2<T>* v) {
   } else if constexpr (N == 3) {
     constexpr T h = (T)(SG * Root<1, 3>::s);
     const C2<T> t = cadd(v[1], v[2]), d = csub(v[1], v[2]);
-    const C2<T> m = {v[0].x - T(0.5) * t.x, v[0].y - T(0.5) * t.y};
+    const C2<T> m = cfma(T(-0.5), t, v[0]);
     v[0] = cadd(v[0], t);
-    v[1] = C2<T>{m.x - h * d.y, m.y + h * d.x};
-    v[2] = C2<T>{m.x + h * d.y, m.y - h * d.x};
+    v[1] = cfma_i(h, d, m);
+    v[2] = cfma_i(-h, d, m);
   } else if constexpr (N == 4) {
     const C2<T> a = cadd(v[0], v[2]), b = csub(v[0], v[2]);
     const C2<T> c = cadd(v[1], v[3]), d = rot<SG, 1, 4>(csub(v[1], v[3]));
@@ -114,10 +118,10 @@ __device__ __forceinline__ void rdft(C2<T>* v) {
     const C2<T> a1 = cadd(v[1], v[4]), b1 = csub(v[1], v[4]);
     const C2<T> a2 = cadd(v[2], v[3]), b2 = csub(v[2], v[3]);
     const C2<T> x0 = v[0];
-    const C2<T> r1 = {x0.x + c1 * a1.x + c2 * a2.x, x0.y + c1 * a1.y + c2 * a2.y};
-    const C2<T> r2 = {x0.x + c2 * a1.x + c1 * a2.x, x0.y + c2 * a1.y + c1 * a2.y};
-    const C2<T> q1 = {-(s1 * b1.y + s2 * b2.y), s1 * b1.x + s2 * b2.x};
-    const C2<T> q2 = {-(s2 * b1.y - s1 * b2.y), s2 * b1.x - s1 * b2.x};
+    const C2<T> r1 = cfma(c2, a2, cfma(c1, a1, x0));
+    const C2<T> r2 = cfma(c1, a2, cfma(c2, a1, x0));
+    const C2<T> q1 = {-fma_(s1, b1.y, s2 * b2.y), fma_(s1, b1.x, s2 * b2.x)};
+    const C2<T> q2 = {-fma_(s2, b1.y, -(s1 * b2.y)), fma_(s2, b1.x, -(s1 * b2.x))};
     v[0] = cadd(x0, cadd(a1, a2));
     v[1] = cadd(r1, q1);
     v[4] = csub(r1, q1);
@@ -209,14 +213,8 @@ __device__ __forceinline__ void dft_last(C2<T>* v) {
   }
 }
 
-// float32: the any-length kernel's butterflies (fft.h) with every rounding
-// written out -- which product of a sum goes into a fused multiply-add is the
-// compiler's choice otherwise, and may differ from one kernel to the next.
-#pragma clang fp contract(off)
-
-__device__ __forceinline__ C2<float> xcmul(C2<float> a, C2<float> b) {
-  return {__builtin_fmaf(a.x, b.x, -(a.y * b.y)), __builtin_fmaf(a.y, b.x, a.x * b.y)};
-}
+// float32: the any-length kernel's butterflies (fft.h) for a direction known at
+// compile time.
 // a + SG i d, a - SG i d
 template <int SG>
 __device__ __forceinline__ C2<float> xadd_i(C2<float> a, C2<float> d) {
@@ -302,15 +300,15 @@ __device__ __forceinline__ void xdft16(C2<float>* v) {
     for (int k1 = 0; k1 < 4; ++k1) a[n2][k1] = t[k1];
   }
   const C2<float> w1{c1, s * s1}, w2{r, s * r}, w3{s1, s * c1}, w6{-r, s * r}, w9{-c1, -s * s1};
-  a[1][1] = xcmul(a[1][1], w1);
-  a[1][2] = xcmul(a[1][2], w2);
-  a[1][3] = xcmul(a[1][3], w3);
-  a[2][1] = xcmul(a[2][1], w2);
+  a[1][1] = cmul(a[1][1], w1);
+  a[1][2] = cmul(a[1][2], w2);
+  a[1][3] = cmul(a[1][3], w3);
+  a[2][1] = cmul(a[2][1], w2);
   a[2][2] = C2<float>{-s * a[2][2].y, s * a[2][2].x};
-  a[2][3] = xcmul(a[2][3], w6);
-  a[3][1] = xcmul(a[3][1], w3);
-  a[3][2] = xcmul(a[3][2], w6);
-  a[3][3] = xcmul(a[3][3], w9);
+  a[2][3] = cmul(a[2][3], w6);
+  a[3][1] = cmul(a[3][1], w3);
+  a[3][2] = cmul(a[3][2], w6);
+  a[3][3] = cmul(a[3][3], w9);
 #pragma unroll
   for (int k1 = 0; k1 < 4; ++k1) {
     C2<float> t[4] = {a[0][k1], a[1][k1], a[2][k1], a[3][k1]};
@@ -539,8 +537,7 @@ __device__ __forceinline__ void reg_stages(void* smem, C2<T> (&v)[S::V][S::NV], 
         if constexpr (SG > 0) w.y = -w.y;
 #pragma unroll
         for (int u = 0; u < S::V; ++u) {
-          if constexpr (sizeof(T) == 4) v[u][i * R + r] = xcmul(v[u][i * R + r], w);
-          else v[u][i * R + r] = cmul(v[u][i * R + r], w);
+          v[u][i * R + r] = cmul(v[u][i * R + r], w);
         }
       }
 #pragma unroll
@@ -752,7 +749,7 @@ __device__ __forceinline__ void reg_pass_body(const PassArgs<T>& a, const int bl
               double u = __builtin_fma((double)x.x, d, shift);
               if (a.split) u += (double)x.y;
               out[e] = (T)u;
-              if (a.rho) eacc += (double)rho[i * RL + r] * u;
+              if (a.rho) eacc = __builtin_fma((double)rho[i * RL + r], u, eacc);
             }
           }
       }
