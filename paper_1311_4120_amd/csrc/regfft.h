@@ -799,9 +799,13 @@ __global__ void __launch_bounds__((RegPassShape<T, KIND, R1, R2, R3, R4>::NT)) k
   reg_pass_body<T, KIND, RegSeq<R1, R2, R3, R4>>(a, blockIdx.x);
 }
 
-// The lengths with a kernel of their own, 2 N for the sides N a grid commonly
-// has, and their radices: in float64 the largest that end in few stages, in
-// float32 those of the any-length kernel.
+// The lengths with a kernel of their own and their radices: in float64 the
+// largest that end in few stages, in float32 those of the any-length kernel.
+// They are 40 of the 49 that a grid can have (2 N, N even from 8 to 512, a
+// product of 2, 3 and 5): those that take at most four stages in float32, save
+// 500 = 4 x 5 x 5 x 5.  Of the others (324, 432, 500, 540, 648, 720, 864, 900,
+// 972) float32 needs five stages and more, which the any-length kernel runs in
+// both precisions.
 #define JGB_REG_LENGTHS_F64(X)                                                                                        \
   X(4, 4, 1, 1) X(4, 5, 1, 1) X(4, 6, 1, 1) X(4, 8, 1, 1) X(12, 3, 1, 1) X(4, 10, 1, 1) X(4, 12, 1, 1)               \
   X(12, 5, 1, 1) X(8, 8, 1, 1) X(12, 6, 1, 1) X(8, 10, 1, 1) X(8, 12, 1, 1) X(4, 5, 5, 1) X(12, 3, 3, 1)            \

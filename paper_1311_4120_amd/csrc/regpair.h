@@ -253,7 +253,10 @@ __global__ void __launch_bounds__((PairShape<T, RegSeq<R1, R2, R3, R4>>::NT), 4)
 
 // The lengths with a kernel of their own (float64): a last radix that is the
 // first one, eight line pairs (128-byte rows) within the LDS of a block, and no
-// more than eight values a thread.  Beyond, the any-length kernel is the faster
+// more than eight values a thread.  Of the lengths that meet this, 32 (4 x 2 x 4)
+// and 64 (8 x 8) are left to the any-length kernel although theirs would be the
+// faster (whole evaluations: 16^3 72 us, 69 with it; 32^3 78 and 76; 32 x 128 x
+// 128 145 and 122).  Beyond, the any-length kernel is the faster
 // one (320 points, four pairs: 350 against 381 us at 160^3; 288 points as
 // 12 x 2 x 12: 305 against 375 at 144^3); in float32 it is by what the
 // transforms' own radices leave of the gain (16 x 4 x 5 points: 204 against
