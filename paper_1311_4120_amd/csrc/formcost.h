@@ -7,12 +7,14 @@
 // kernel or the noise of a timing.  Forms and chunks therefore follow from what
 // the plan counts: the times below, in microseconds, are those of the kernels
 // with which plans that timed their forms gave the results that programs know
-// (the present gather, rings and tiles load a batch ahead and are faster), fitted to 955 3D node sets of 16^3 to 256^3 points, 64 to 4 million
-// half-set nodes and 5 to 8 taps, each form and chunk of which was timed twice.
-// Where both timings of a node set took the same, the costs take it too for 94%
-// of 385 node sets of common sizes and all of 120 planar ones (not fitted), and
-// 88% of a grid of 282 sparse, dense and elongated ones; where they do not, the
-// choices lay within a few percent of each other, mostly the noise of a timing.
+// (the present gather, rings and tiles load a batch ahead and are faster),
+// fitted to 1329 3D node sets of 16^3 to 256^3 points, 64 to 4 million half-set
+// nodes, 4 to 8 taps and the Gaussian's 12, each form and chunk of which was
+// timed twice.  Where both timings of a node set took the same, the costs take
+// it too for 94% of 385 node sets of common sizes and all of 120 planar ones
+// (not fitted), and 88% of a grid of 282 sparse, dense and elongated ones; where
+// they do not, the choices lay within a few percent of each other, mostly the
+// noise of a timing.
 // The staged interpolation's chunk moves no result by more than the rounding of
 // E's float64 sum and is still timed.
 #pragma once
@@ -56,22 +58,30 @@ inline double beyond(const Nodes& n, double mb) {
   return r / (r + mb);
 }
 
+// 16-byte pieces of a record that each lane of the gather and the rings copies,
+// against the two of 5 to 10 taps.
+inline double pieces(const Nodes& n) { return std::ceil(std::ceil((3 * n.width + 3) / 4) / 4) - 2; }
+
 inline double gather(const Nodes& n, const Items& it) {
-  return 7.88 + either(2.89e-5 * n.entries + 0.00178 * it.count, 0.01415 * (1 + 1.01 * beyond(n, 4.51)) * it.longest, 4) +
-         partials(it, 1.05, 0.00655, 0.107);
+  const double f = 1 + 0.09 * pieces(n);
+  return 7.86 + either(2.88e-5 * f * n.entries + 0.00177 * it.count, 0.01415 * f * (1 + 0.98 * beyond(n, 4.63)) * it.longest, 4) +
+         partials(it, 1.1, 0.00587, 0.109);
 }
 inline double rings(const Nodes& n, const Items& it) {
-  return 8.6 + either(2.26e-5 * n.ring_entries + 7.31e-5 * n.rings + 0.008 * it.count, 0.0512 * it.longest, 10) +
-         partials(it, 1.51, 0.0084, 0.106);
+  const double f = 1 + 0.097 * pieces(n);
+  return 8.64 + either(f * (2.29e-5 * n.ring_entries + 7.04e-5 * n.rings) + 0.008 * it.count, 0.0515 * f * it.longest, 10) +
+         partials(it, 1.64, 0.00773, 0.097);
 }
 // it: the items of the untuned gather, whose lists the tiles then shared
 inline double tiles(const Nodes& n, const Items& it) {
-  return 7.64 + either(1.76e-6 * n.entries * n.width + 0.00253 * it.count,
-                       0.00413 * (1 + 3.09 * beyond(n, 0.0107)) * it.longest, 5) +
-         std::max(2.3e-5 * n.nodes, 1.07e-5 * n.entries) + 0.152 * n.entries / n.nodes;
+  const bool wide = n.width > 8;  // the twelve taps of the Gaussian
+  return 7.83 + either(1.69e-6 * (wide ? 0.7 : 1.0) * n.entries * n.width + 0.00254 * it.count,
+                       0.00341 * (wide ? 1.05 : 1.0) * (1 + 3.92 * beyond(n, 0.0116)) * it.longest, 5) +
+         std::max(2.3e-5 * n.nodes, 1.11e-5 * n.entries) + 0.119 * n.entries / n.nodes;
 }
 inline double staged(const Nodes& n, double count, double longest) {
-  return 8.2 + either(3.59e-5 * n.nodes * std::sqrt(n.width) + 0.0129 * count, 0.0268 * longest, 5);
+  if (n.width > 8) return 10.4 + either(3.09e-4 * n.nodes + 0.0316 * count, 0.0709 * longest, 5);
+  return 8.2 + either(3.55e-5 * n.nodes * std::sqrt(n.width) + 0.0129 * count, 0.0266 * longest, 5);
 }
 
 // Ring items from which on the two longest chunks cost the same: with 21 254 of

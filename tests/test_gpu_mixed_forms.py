@@ -8,7 +8,8 @@ import pytest
 pytestmark = pytest.mark.gpu
 import torch  # noqa: E402, F401
 
-# grid, nodes, eps, Algorithm 2, tiles, gather chunk (negative: rings)
+# grid, nodes, eps ("gauss": the Gaussian's 12 taps), Algorithm 2, tiles, gather
+# chunk (negative: rings)
 SETS = [
     ((16, 16, 16), (20, 10, 20), 1e-5, False, True, 256),
     ((24, 24, 24), (31, 15, 30), 1e-6, False, True, 256),
@@ -35,6 +36,15 @@ SETS = [
     ((64, 64, 64), (40, 32, 64), 1e-4, True, False, 512),
     ((128, 128, 128), (40, 32, 64), 1e-6, True, False, -1024),
     ((256, 256, 256), (256, 128, 256), 1e-5, False, True, -8192),
+    ((32, 32, 32), (32, 16, 32), "gauss", False, True, 256),
+    ((48, 48, 48), (33, 16, 32), "gauss", False, False, 256),
+    ((64, 64, 64), (64, 32, 64), "gauss", False, False, -2048),
+    ((96, 96, 96), (96, 48, 96), "gauss", False, True, -4096),
+    ((90, 60, 108), (108, 54, 108), "gauss", False, True, -4096),
+    ((128, 128, 128), (40, 32, 64), "gauss", True, False, -1024),
+    ((64, 64, 64), (64, 32, 64), 1e-2, False, False, 512),
+    ((96, 96, 96), (96, 48, 96), 1e-2, False, False, 1024),
+    ((160, 144, 160), (208, 104, 208), 1e-2, False, True, -8192),
 ]
 
 
@@ -42,8 +52,9 @@ SETS = [
 def test_form(n, nodes, eps, split, tiles, chunk, monkeypatch):
     import paper_1311_4120_amd as jgb
     monkeypatch.delenv("JGB_AUTOTUNE_CACHE", raising=False)
-    plan = jgb.Plan(n, tuple(0.15 * v for v in n), "dipole3d", nodes, eps=eps, precision="mixed",
-                    axis=(0.48, 0.6, 0.64), theta_rule="costheta" if split or n[0] == 256 else "theta", split=split,
+    gauss = eps == "gauss"
+    plan = jgb.Plan(n, tuple(0.15 * v for v in n), "dipole3d", nodes, eps=1e-5 if gauss else eps, precision="mixed",
+                    gaussian_kernel=gauss, axis=(0.48, 0.6, 0.64), theta_rule="costheta" if split or n[0] == 256 else "theta", split=split,
                     autotune=True)
     got = plan.info["interp_chunk"] == 0, plan.info["spread_chunk"]
     plan.close()
