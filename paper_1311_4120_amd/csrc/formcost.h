@@ -8,13 +8,13 @@
 // the plan counts: the times below, in microseconds, are those of the kernels
 // with which plans that timed their forms gave the results that programs know
 // (the present gather, rings and tiles load a batch ahead and are faster),
-// fitted to 1329 3D node sets of 16^3 to 256^3 points, 64 to 4 million half-set
+// fitted to some 1950 3D node sets of 16^3 to 256^3 points, 64 to 4 million half-set
 // nodes, 4 to 8 taps and the Gaussian's 12, each form and chunk of which was
 // timed twice.  Where both timings of a node set took the same, the costs take
-// it too for 94% of 385 node sets of common sizes and all of 120 planar ones
-// (not fitted), and 88% of a grid of 282 sparse, dense and elongated ones; where
-// they do not, the choices lay within a few percent of each other, mostly the
-// noise of a timing.
+// it too for 95% of 1023 node sets of common sizes (94% of those that a fit to
+// the others left out), all of 120 planar ones (not fitted), and 86% of a grid of
+// 282 sparse, dense and elongated ones; where they do not, the choices lay within
+// a few percent of each other, mostly the noise of a timing.
 // The staged interpolation's chunk moves no result by more than the rounding of
 // E's float64 sum and is still timed.
 #pragma once
@@ -52,10 +52,10 @@ inline double partials(const Items& it, double start, double slot, double chain)
   return it.slots > 0 ? start + std::max(slot * it.slots, chain * it.most) : 0.0;
 }
 
-// 0 .. 1: how much of the nodes' records (MB) lies beyond the caches.
-inline double beyond(const Nodes& n, double mb) {
-  const double r = n.nodes * (3 * n.width + 3) * 4e-6;
-  return r / (r + mb);
+// 0 .. 1: how far the nodes' records (MB) outgrow a cache of `mb`; the larger
+// `sharp`, the sharper the turn (4 MB of L2 per XCD for the gather and the rings).
+inline double beyond(const Nodes& n, double mb, double sharp) {
+  return 1.0 / (1.0 + std::pow(mb / (n.nodes * (3 * n.width + 3) * 4e-6), sharp));
 }
 
 // 16-byte pieces of a record that each lane of the gather and the rings copies,
@@ -63,25 +63,26 @@ inline double beyond(const Nodes& n, double mb) {
 inline double pieces(const Nodes& n) { return std::ceil(std::ceil((3 * n.width + 3) / 4) / 4) - 2; }
 
 inline double gather(const Nodes& n, const Items& it) {
-  const double f = 1 + 0.09 * pieces(n);
-  return 7.86 + either(2.88e-5 * f * n.entries + 0.00177 * it.count, 0.01415 * f * (1 + 0.98 * beyond(n, 4.63)) * it.longest, 4) +
-         partials(it, 1.1, 0.00587, 0.109);
+  const double f = 1 + 0.112 * pieces(n);
+  return 7.71 + either(2.91e-5 * f * n.entries + 0.00175 * it.count, 0.01538 * f * (1 + 0.66 * beyond(n, 4.13, 5)) * it.longest, 4) +
+         partials(it, 1.36, 0.00175, 0.111);
 }
 inline double rings(const Nodes& n, const Items& it) {
-  const double f = 1 + 0.097 * pieces(n);
-  return 8.64 + either(f * (2.29e-5 * n.ring_entries + 7.04e-5 * n.rings) + 0.008 * it.count, 0.0515 * f * it.longest, 10) +
-         partials(it, 1.64, 0.00773, 0.097);
+  const double f = 1 + 0.091 * pieces(n);
+  return 8.77 + either(f * (2.23e-5 * n.ring_entries + 7.7e-5 * n.rings) + 0.00782 * it.count,
+                       0.0483 * f * (1 + 0.086 * beyond(n, 3.7, 35)) * it.longest, 10) +
+         partials(it, 1.8, 0.00812, 0.0936);
 }
 // it: the items of the untuned gather, whose lists the tiles then shared
 inline double tiles(const Nodes& n, const Items& it) {
   const bool wide = n.width > 8;  // the twelve taps of the Gaussian
-  return 7.83 + either(1.69e-6 * (wide ? 0.7 : 1.0) * n.entries * n.width + 0.00254 * it.count,
-                       0.00341 * (wide ? 1.05 : 1.0) * (1 + 3.92 * beyond(n, 0.0116)) * it.longest, 5) +
-         std::max(2.3e-5 * n.nodes, 1.11e-5 * n.entries) + 0.119 * n.entries / n.nodes;
+  return 7.78 + either(1.72e-6 * (wide ? 0.7 : 1.0) * n.entries * n.width + 0.00255 * it.count,
+                       0.00348 * (wide ? 1.06 : 1.0) * (1 + 3.8 * beyond(n, 0.0106, 1)) * it.longest, 5) +
+         std::max(2.3e-5 * n.nodes, 1.08e-5 * n.entries) + 0.125 * n.entries / n.nodes;
 }
 inline double staged(const Nodes& n, double count, double longest) {
-  if (n.width > 8) return 10.4 + either(3.09e-4 * n.nodes + 0.0316 * count, 0.0709 * longest, 5);
-  return 8.2 + either(3.55e-5 * n.nodes * std::sqrt(n.width) + 0.0129 * count, 0.0266 * longest, 5);
+  if (n.width > 8) return 10.4 + either(3.08e-4 * n.nodes + 0.0316 * count, 0.071 * longest, 5);
+  return 8.18 + either(3.55e-5 * n.nodes * std::sqrt(n.width) + 0.0129 * count, 0.027 * longest, 5);
 }
 
 // Ring items from which on the two longest chunks cost the same: with 21 254 of
